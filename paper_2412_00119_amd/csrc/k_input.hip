@@ -14,32 +14,117 @@ namespace bmlp {
 namespace {
 
 constexpr int kStreamExpand = 5;
-constexpr int kFeat = 64;   // features per work-group of the median kernel
+// The median of kMedFeat neighbouring features per work-group, from 256-bin
+// histograms in LDS.
+//
+// What bounds it: each feature's whole column is counted by one work-group
+// (there is no scratch memory to merge partial counts in), so a compute unit
+// takes n cache lines, one per row, and the line fills (two cycles each)
+// are what is left.  To get there the counting must cost less than that:
+//   * a lane loads its row's kMedFeat bytes at once, and a thread has
+//     kMedRows rows in flight (16 waves: enough to cover memory latency);
+//   * the histograms are kept kMedCopies times, bin-major, one LDS bank per
+//     (copy, feature) slot, and lane l counts its bytes in the rotated order
+//     l, l + 1, ... (mod kMedFeat) into the copy l / kMedFeat.  So the 64
+//     lanes of every atomic are in 64 different banks, whatever the data
+//     (features with few distinct values included);
+//   * an atomic's address is one v_perm_b32: byte 0 the slot, byte 1 the
+//     value.
+// The work-groups of one XCD take neighbouring features, so a row's cache
+// line is fetched into one or two L2s instead of all eight.
+// 60000 x 784 (47 MB): 3810 -> 75 us (the kernel before had a work-group of
+// 256 threads per 64 features, one byte load per thread in flight).
+constexpr int kMedFeat = 8;
+constexpr int kMedCopies = 64 / kMedFeat;
+constexpr int kMedThreads = 1024;
+constexpr int kMedRows = 8;      // rows per thread and pass
 
-// One work-group per 64 features: a 256-bin histogram of each feature in
-// LDS over all N rows (four rows per pass, 64 features each, one byte
-// load per thread), then the first value whose running count reaches
-// floor((N - 1) / 2) + 1.
-__global__ __launch_bounds__(256) void feature_median_kernel(const int8_t *__restrict__ x, int n, int K,
-                                                             int8_t *__restrict__ med) {
-  __shared__ uint32_t hist[kFeat][256];
-  const int f0 = blockIdx.x * kFeat;
-  for (int i = threadIdx.x; i < kFeat * 256; i += 256) (&hist[0][0])[i] = 0u;
+// the 8 bytes at p (any alignment)
+__device__ __forceinline__ uint2 load8(const int8_t *p) {
+  uint2 v;
+  __builtin_memcpy(&v, p, 8);
+  return v;
+}
+
+__global__ __launch_bounds__(kMedThreads) void feature_median_kernel(const int8_t *__restrict__ x, int n, int K,
+                                                                     int8_t *__restrict__ med, int per_xcd) {
+  __shared__ uint32_t hist[256][64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  // XCD b % 8 takes the tiles [per_xcd * (b % 8), + per_xcd)
+  const int tile = per_xcd * ((int)blockIdx.x & 7) + ((int)blockIdx.x >> 3);
+  // the last tile starts early enough to stay inside the row (its first
+  // features are then counted twice, with the same result)
+  const int f0 = max(0, min(tile * kMedFeat, K - kMedFeat));
+  if (tile * kMedFeat >= K) return;
+  for (int i = tid; i < 256 * 64 / 4; i += kMedThreads) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  const int f = threadIdx.x & (kFeat - 1), r0 = threadIdx.x / kFeat;
-  if (f0 + f < K) {
-    for (int r = r0; r < n; r += 256 / kFeat) atomicAdd(&hist[f][x[(size_t)r * K + f0 + f] + 128], 1u);
+  const int rot = lane % kMedFeat, copy0 = lane - rot;
+  uint32_t slot[kMedFeat];   // byte address of the slot within a bin, per step
+#pragma unroll
+  for (int j = 0; j < kMedFeat; ++j) slot[j] = 4u * (uint32_t)(copy0 + (rot + j) % kMedFeat);
+  uint8_t *const base = reinterpret_cast<uint8_t *>(hist);
+  auto count = [&](uint2 v) {
+    // value + 128 per byte, then the bytes rotated by rot
+    uint64_t w = ((uint64_t)(v.y ^ 0x80808080u) << 32) | (v.x ^ 0x80808080u);
+    if (rot) w = (w >> (8 * rot)) | (w << (64 - 8 * rot));
+    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+#pragma unroll
+    for (int j = 0; j < kMedFeat; ++j) {
+      // bytes: [slot, value, 0, 0] (selector 0x0C gives a zero byte, 0 the
+      // second source's byte 0, 4 + b the first source's byte b)
+      const uint32_t addr = __builtin_amdgcn_perm(j < 4 ? lo : hi, slot[j], 0x0C0C0000u | ((4u + (j & 3)) << 8));
+      atomicAdd(reinterpret_cast<uint32_t *>(base + addr), 1u);
+    }
+  };
+  if (K >= kMedFeat) {
+    const int8_t *xf = x + f0;
+    const uint32_t rows = (uint32_t)n;
+    uint32_t r = (uint32_t)tid;
+    for (; r + (kMedRows - 1) * kMedThreads < rows; r += kMedRows * kMedThreads) {
+      uint2 v[kMedRows];
+#pragma unroll
+      for (int q = 0; q < kMedRows; ++q) v[q] = load8(xf + (size_t)(r + q * kMedThreads) * K);
+#pragma unroll
+      for (int q = 0; q < kMedRows; ++q) count(v[q]);
+    }
+    for (; r < rows; r += kMedThreads) count(load8(xf + (size_t)r * K));
+  } else {   // rows of fewer bytes than a load
+    for (uint32_t r = (uint32_t)tid; r < (uint32_t)n; r += kMedThreads)
+      for (int f = 0; f < K; ++f) atomicAdd(&hist[(int)x[(size_t)r * K + f] + 128][copy0 + f], 1u);
   }
   __syncthreads();
-  if (threadIdx.x < kFeat && f0 + threadIdx.x < K) {
+  // one wave per feature: lane l sums the copies of bins 4l .. 4l + 3, the
+  // wave scans, and the lane in whose bins the running count reaches
+  // floor((n - 1) / 2) + 1 writes the value
+  const int f = tid >> 6;
+  if (f < kMedFeat && f0 + f < K) {
     const uint32_t want = (uint32_t)((n - 1) / 2) + 1u;
-    uint32_t run = 0u;
-    int v = 0;
-    for (; v < 256; ++v) {
-      run += hist[threadIdx.x][v];
-      if (run >= want) break;
+    uint32_t c[4], own = 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      c[q] = 0u;
+      // each lane starts at a copy of its own (spreads the banks)
+#pragma unroll
+      for (int k = 0; k < kMedCopies; ++k) c[q] += hist[4 * lane + q][((lane + k) % kMedCopies) * kMedFeat + f];
+      own += c[q];
     }
-    med[f0 + threadIdx.x] = (int8_t)(v - 128);
+    uint32_t run = own;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const uint32_t v = (uint32_t)__shfl_up((int)run, d, 64);
+      if (lane >= d) run += v;
+    }
+    uint32_t before = run - own;
+    if (before < want && run >= want) {
+      int v = 4 * lane;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        before += c[q];
+        if (before < want) ++v;
+        else break;
+      }
+      med[f0 + f] = (int8_t)(v - 128);
+    }
   }
 }
 
@@ -163,7 +248,8 @@ __global__ __launch_bounds__(256) void expand_kernel(const int8_t *__restrict__ 
 
 hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, hipStream_t s) {
   if (n <= 0 || K <= 0) return hipSuccess;
-  hipLaunchKernelGGL(feature_median_kernel, dim3((K + kFeat - 1) / kFeat), dim3(256), 0, s, x, n, K, med);
+  const int per_xcd = ((K + kMedFeat - 1) / kMedFeat + 7) / 8;   // tiles of each XCD
+  hipLaunchKernelGGL(feature_median_kernel, dim3(8 * per_xcd), dim3(kMedThreads), 0, s, x, n, K, med, per_xcd);
   return hipGetLastError();
 }
 
