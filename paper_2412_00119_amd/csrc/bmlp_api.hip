@@ -308,7 +308,7 @@ int bmlp_attach(const bmlp_config *cfg, void *d_state, void *d_workspace, void *
 int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void *stream) {
   if (n < 0 || K < 1 || n > 65535) return BMLP_ESHAPE;
   if (n > 0 && (d_pm1 == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_pack(d_pm1, n, K, d_bits, as_stream(stream)));
+  BMLP_LAUNCH(launch_binarize(d_pm1, n, K, nullptr, d_bits, as_stream(stream)));
   return BMLP_OK;
 }
 

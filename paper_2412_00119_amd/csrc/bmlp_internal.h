@@ -29,8 +29,6 @@ constexpr int kRawRsrcWord3 = 0x00020000;
 // Launchers (each returns hipSuccess or the launch error).
 // ---------------------------------------------------------------------------
 
-hipError_t launch_pack(const int8_t *x, int n, int K, uint64_t *bits, hipStream_t s);
-
 // H_l and W_l of one layer from Philox stream 1 (init) or W_l from the H_l in
 // place (attach); P_l from stream 2.
 hipError_t launch_read_h(const uint8_t *H, int ld_h, int h_ps, int bound, int k_in, int k_out,
@@ -149,7 +147,8 @@ hipError_t launch_gather_batch(const uint64_t *x_all, const int32_t *y_all, int 
                                const int32_t *order, int n, uint64_t *xb, int32_t *yb, hipStream_t s);
 
 // The input side (int8 features): per-feature lower median over n rows;
-// bit = (x >= thr) rows; the fixed random ±1 expansion layer sign(x R^T).
+// bit = (x >= thr) rows (thr null: 1 everywhere, i.e. x > 0, which packs ±1
+// rows); the fixed random ±1 expansion layer sign(x R^T).
 hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, hipStream_t s);
 hipError_t launch_binarize(const int8_t *x, int n, int K, const int8_t *thr, uint64_t *bits, hipStream_t s);
 hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t seed, uint64_t *bits, hipStream_t s);

@@ -2,7 +2,7 @@
 // footnote 1), for integer features (int8):
 //   * the median of every feature over a reference set (the lower middle
 //     order statistic, so an element of the column and exact);
-//   * median binarisation: bit = (x >= median);
+//   * median binarisation: bit = (x >= median); the same kernel packs ±1 rows;
 //   * the fixed random ±1 expansion layer: bit = (sum_i x_i R[j][i] >= 0),
 //     exact in int32, with R drawn from Philox stream 5 (counter layer word
 //     2^32 - 1, t = 0): element e = j K_raw + i is bit (e & 127) of block
@@ -128,17 +128,76 @@ __global__ __launch_bounds__(kMedThreads) void feature_median_kernel(const int8_
   }
 }
 
-// one wave per 64-bit output word: lane i tests column 64 w + i
+// Bit rows from int8 rows: bit = (x >= threshold of the column), the
+// thresholds a row of int8 (median binarisation) or, with PM1, 1 everywhere
+// (x > 0: packing ±1 rows).
+//
+// Bound by the read of x.  A lane takes 16 neighbouring columns with one
+// 16-byte load (any alignment) and stores their 16 bits; its thresholds stay
+// in registers while it walks kBinRows rows, whose loads are all issued
+// before the first is used.  Four bytes are compared with two subtractions:
+// with x and t biased to unsigned bytes and spread to 16-bit halves, bit 8
+// of (x | 0x100) - t is set iff x >= t, and no half borrows from the other.
+// A wave covers 64 / lpr rows by lpr lanes each (lpr a power of two, at most
+// 64), so that narrow rows do not leave lanes idle.
+// 60000 x 784 (47 MB): 107 -> 12.3 us; the kernel before took one byte per
+// lane and one 64-bit word per wave.
+constexpr int kBinRows = 4;
+
+struct BinLane {
+  uint32_t te[4], to[4];   // thresholds of the even and odd bytes, biased, in 16-bit halves
+};
+
+// bits 0..3: x >= threshold for the four bytes of w (dword q of the lane's 16)
+__device__ __forceinline__ uint32_t ge4(uint32_t w, const BinLane &t, int q) {
+  const uint32_t v = w ^ 0x80808080u;
+  const uint32_t e = ((v & 0x00FF00FFu) | 0x01000100u) - t.te[q];          // bytes 0, 2 -> bits 8, 24
+  const uint32_t o = (((v >> 8) & 0x00FF00FFu) | 0x01000100u) - t.to[q];   // bytes 1, 3 -> bits 8, 24
+  const uint32_t m = ((e >> 8) & 0x00010001u) | ((o >> 7) & 0x00020002u);  // bits 0, 1, 16, 17
+  return (m | (m >> 14)) & 0xFu;
+}
+
+template <bool PM1>
 __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict__ x, int n, int K, int words,
-                                                       const int8_t *__restrict__ thr, uint64_t *__restrict__ bits) {
-  const int row = blockIdx.y;
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= n || w >= words) return;   // whole wave leaves together
-  const int col = w * 64 + lane;
-  const bool pos = col < K && x[(size_t)row * K + col] >= thr[col];
-  const uint64_t m = __ballot(pos);
-  if (lane == 0) bits[(size_t)row * words + w] = m;
+                                                       const int8_t *__restrict__ thr, uint64_t *__restrict__ bits,
+                                                       int lpr_log) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lpr = 1 << lpr_log, rpw = 64 >> lpr_log;          // lanes per row, rows per wave
+  const int unit = (int)blockIdx.x * lpr + (lane & (lpr - 1));   // 16 columns of the row
+  if (unit >= 4 * words) return;
+  const int col = 16 * unit;
+  uint16_t *out = reinterpret_cast<uint16_t *>(bits) + unit;
+  const int row0 = ((int)blockIdx.y * 4 + wave) * (kBinRows * rpw) + (lane >> lpr_log);
+  if (col + 16 <= K) {
+    BinLane t;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      uint32_t w = 0x01010101u;
+      if constexpr (!PM1) __builtin_memcpy(&w, thr + col + 4 * q, 4);
+      w ^= 0x80808080u;
+      t.te[q] = w & 0x00FF00FFu;
+      t.to[q] = (w >> 8) & 0x00FF00FFu;
+    }
+    uint4 v[kBinRows];
+#pragma unroll
+    for (int i = 0; i < kBinRows; ++i) __builtin_memcpy(&v[i], x + (size_t)min(row0 + i * rpw, n - 1) * K + col, 16);
+#pragma unroll
+    for (int i = 0; i < kBinRows; ++i) {
+      const int row = row0 + i * rpw;
+      if (row < n)
+        out[(size_t)row * 4 * words] = (uint16_t)(ge4(v[i].x, t, 0) | (ge4(v[i].y, t, 1) << 4) |
+                                                  (ge4(v[i].z, t, 2) << 8) | (ge4(v[i].w, t, 3) << 12));
+    }
+  } else {   // the row's end: byte loads, and zeros past column K
+    for (int i = 0; i < kBinRows; ++i) {
+      const int row = row0 + i * rpw;
+      if (row >= n) break;
+      uint32_t m = 0u;
+      for (int c = 0; c < 16 && col + c < K; ++c)
+        m |= (uint32_t)(x[(size_t)row * K + col + c] >= (PM1 ? (int8_t)1 : thr[col + c])) << c;
+      out[(size_t)row * 4 * words] = (uint16_t)m;
+    }
+  }
 }
 
 // bits e .. e + 31 of stream 5 (32 consecutive elements; they straddle at
@@ -256,7 +315,14 @@ hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, hip
 hipError_t launch_binarize(const int8_t *x, int n, int K, const int8_t *thr, uint64_t *bits, hipStream_t s) {
   if (n <= 0 || K <= 0) return hipSuccess;
   const int words = (K + 63) / 64;
-  hipLaunchKernelGGL(binarize_kernel, dim3((words + 3) / 4, n), dim3(256), 0, s, x, n, K, words, thr, bits);
+  int lpr_log = 2;   // a row has 4 words units of 16 columns
+  while (lpr_log < 6 && (1 << lpr_log) < 4 * words) ++lpr_log;
+  const int rows = 4 * kBinRows * (64 >> lpr_log);   // rows of a work-group
+  const dim3 grid((4 * words + (1 << lpr_log) - 1) >> lpr_log, (n + rows - 1) / rows);
+  if (thr != nullptr)
+    hipLaunchKernelGGL((binarize_kernel<false>), grid, dim3(256), 0, s, x, n, K, words, thr, bits, lpr_log);
+  else
+    hipLaunchKernelGGL((binarize_kernel<true>), grid, dim3(256), 0, s, x, n, K, words, thr, bits, lpr_log);
   return hipGetLastError();
 }
 

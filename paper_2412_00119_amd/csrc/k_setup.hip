@@ -1,23 +1,9 @@
-// Setup kernels: bit packing of ±1 inputs, state initialisation, fills.
+// Setup kernels: state initialisation, reading H back, fills.
 #include "bmlp_internal.h"
 #include "philox.h"
 
 namespace bmlp {
 namespace {
-
-// One wave per 64-value chunk of a row: lane i tests value (w*64 + i) and the
-// wave ballot is the packed word.  Grid: (ceil(words/4), n), 256 threads.
-__global__ __launch_bounds__(256) void pack_kernel(const int8_t *__restrict__ x, int n, int K,
-                                                   int words, uint64_t *__restrict__ bits) {
-  const int row = blockIdx.y;
-  const int w = blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (row >= n || w >= words) return;     // whole wave leaves together
-  const int col = w * 64 + lane;
-  const bool pos = col < K && x[(size_t)row * K + col] > 0;
-  const uint64_t m = __ballot(pos);
-  if (lane == 0) bits[(size_t)row * words + w] = m;
-}
 
 // Bit (j & 127) of Philox block j >> 7 of the given layer/stream at step 0.
 __device__ __forceinline__ bool stream_bit(uint64_t j, uint64_t seed, int layer, uint32_t stream) {
@@ -112,13 +98,6 @@ __global__ __launch_bounds__(256) void fill_rows_kernel(int32_t *p, int rows, in
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }
 
 }  // namespace
-
-hipError_t launch_pack(const int8_t *x, int n, int K, uint64_t *bits, hipStream_t s) {
-  const int words = cdiv(K, 64);
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(pack_kernel, dim3(cdiv(words, 4), n), dim3(256), 0, s, x, n, K, words, bits);
-  return hipGetLastError();
-}
 
 hipError_t launch_init_h(uint8_t *H, int ld_h, int h_ps, int bound, uint64_t *W, int words_in, int k_in,
                          int k_out, uint64_t seed, int layer, bool from_h, hipStream_t s) {

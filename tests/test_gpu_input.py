@@ -34,6 +34,31 @@ def test_median_and_binarize(n, k):
                                   pack_np(ob.median_binarize(x, m), bits.shape[1]))
 
 
+@pytest.mark.parametrize("n,k", [(3, 7), (4, 8), (5, 9), (1023, 15), (8192, 16), (8193, 17), (17500, 23), (40, 1040),
+                                 (130, 1025)])
+def test_median_and_binarize_edges(n, k):
+    """Feature tiles that overlap at the end of a row, rows shorter than a
+    load, row counts around the passes of a work-group, rows that start at
+    any byte, and columns of extreme or few values."""
+    torch = torch_cuda()
+    rng = np.random.default_rng(7 * n + k)
+    x = _int8(rng, (n, k))
+    x[:, 0] = np.where(rng.random(n) < 0.5, -128, 127)
+    x[:, k - 1] = rng.integers(-1, 2, n)
+    note(f"median edges n={n} k={k}")
+    xd = torch.from_numpy(x).cuda()
+    med = B.feature_median(xd)
+    bits = B.binarize(xd, med)
+    packed = torch.empty_like(bits)
+    B.bmlp_pack(xd.data_ptr(), n, k, packed.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    m = ob.feature_median(x)
+    np.testing.assert_array_equal(med.cpu().numpy(), m)
+    np.testing.assert_array_equal(bits.cpu().numpy().view(np.uint64),
+                                  pack_np(ob.median_binarize(x, m), bits.shape[1]))
+    np.testing.assert_array_equal(packed.cpu().numpy().view(np.uint64), pack_np(x, bits.shape[1]))
+
+
 @pytest.mark.parametrize("n,k_raw,k0", [(5, 1, 64), (300, 37, 100), (70, 300, 257), (257, 5000, 64),
                                         (64, 4096, 128)])
 def test_expand(n, k_raw, k0):
