@@ -200,105 +200,215 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
   }
 }
 
-// bits e .. e + 31 of stream 5 (32 consecutive elements; they straddle at
-// most two Philox blocks)
-__device__ uint32_t expand_bits32(uint64_t e, uint32_t k0, uint32_t k1) {
-  const uint32_t blk = (uint32_t)(e >> 7), off = (uint32_t)(e & 127);
-  const U32x4 a = philox4x32_10(blk, 0xFFFFFFFFu, 0u, kStreamExpand, k0, k1);
-  const uint32_t wi = off >> 5, sh = off & 31;
-  const uint32_t lo = pick_word(a, wi);
-  uint32_t hi;
-  if (wi < 3) {
-    hi = pick_word(a, wi + 1);
-  } else {
-    const U32x4 b = philox4x32_10(blk + 1u, 0xFFFFFFFFu, 0u, kStreamExpand, k0, k1);
-    hi = b.x;
-  }
-  return sh ? (lo >> sh) | (hi << (32 - sh)) : lo;
+// The expansion layer on the int8 matrix cores (v_mfma_i32_32x32x32_i8).
+//
+// A work-group computes 128 patterns x 128 output columns with four waves of
+// 64 x 64, and walks the row tiles blockIdx.y, + gridDim.y, ... of its
+// columns.  Bound by the matrix cores' feed: per MFMA a wave spends about four
+// vector instructions on operands, so both are made cheaply.
+//   * R's weights enter as the bit alone, r = (w + 1) / 2 in {0, 1}: byte b
+//     of operand dword s of a 32-bit word is bit 8b + s, (word >> s) &
+//     0x01010101, two instructions per four weights straight from R's bits;
+//     then sum_i x_i w_i = 2 acc - sum_i x_i, the row sums of x added up
+//     (v_dot4_i32_i8) as x is staged.
+//   * x is staged through LDS with the bytes of each 32 inputs transposed to
+//     match (dword s holds inputs s, s + 8, s + 16, s + 24), 16 v_perm_b32
+//     per 32 bytes once for all columns.  Rows are 128 + 16 bytes apart, so
+//     that 16-byte reads at one row per lane hit every bank once; the next
+//     stage's global loads are in flight while one is computed.
+//   * R's bits for kXChunk inputs of the 128 columns are drawn into LDS as
+//     whole Philox blocks; the columns' bit offsets in them are taken out by
+//     one v_alignbit_b32 per word read.  They are drawn once per work-group
+//     when all inputs fit one chunk.
+// Exact: |acc| <= 128 * 65536.
+// 10000 x 784 -> 3072: 1342 -> 52 us (the kernel before summed 4 inputs at a
+// time with v_dot4_i32_i8, rebuilding the +-1 bytes for every pattern).
+typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v16i __attribute__((ext_vector_type(16)));
+
+constexpr int kXTile = 128;                      // patterns and output columns of a tile
+constexpr int kXStage = 128;                     // inputs per LDS stage
+constexpr int kXChunk = 1024;                    // inputs whose R bits are in LDS at once
+constexpr int kXLd = kXStage + 16;               // bytes between staged rows
+constexpr int kXBlocks = kXChunk / 128 + 1;      // Philox blocks covering a chunk of a column
+constexpr int kXWords = 4 * kXBlocks + 1;        // words between columns (odd: banks spread)
+
+// byte s of a, b, c, d as one dword, for s = 0..3
+__device__ __forceinline__ uint4 transpose4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t ab_lo = __builtin_amdgcn_perm(b, a, 0x05010400u);   // a0 b0 a1 b1
+  const uint32_t ab_hi = __builtin_amdgcn_perm(b, a, 0x07030602u);   // a2 b2 a3 b3
+  const uint32_t cd_lo = __builtin_amdgcn_perm(d, c, 0x05010400u);
+  const uint32_t cd_hi = __builtin_amdgcn_perm(d, c, 0x07030602u);
+  return make_uint4(__builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u), __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u),
+                    __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u), __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u));
 }
 
-constexpr int kXCols = 64;    // output columns (R rows) per work-group
-constexpr int kXRows = 64;    // patterns per pass
-constexpr int kXWords = 128;  // R words per column held in LDS (4096 inputs)
+// v_writelane_b32 (see the forward kernel)
+extern "C" __device__ uint32_t bmlp_input_writelane(uint32_t v, uint32_t lane, uint32_t old)
+    __asm("llvm.amdgcn.writelane.i32");
 
-// Work-group: 64 output columns j0 .. j0 + 63 and a chunk of patterns.
-// The columns' R rows are made once, as bits in LDS (in passes of 4096
-// inputs); thread (pattern p, column group g) sums 16 columns with sdot4 on
-// 4 int8 inputs and 4 ±1 bytes at a time.
-__global__ __launch_bounds__(256) void expand_kernel(const int8_t *__restrict__ x, int n, int k_raw, int k0,
-                                                     uint64_t seed, int rows_per_block, uint64_t *__restrict__ bits,
-                                                     int words_out) {
-  __shared__ uint32_t sR[kXCols][kXWords + 1];
-  __shared__ int32_t sZ[kXRows][kXCols + 1];
-  const int j0 = blockIdx.x * kXCols;
-  const int p0 = blockIdx.y * rows_per_block;
-  const int p1 = min(n, p0 + rows_per_block);
+__global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict__ x, int n, int k_raw, int k0,
+                                                        uint64_t seed, uint32_t *__restrict__ bits, int words32) {
+  __shared__ __align__(16) uint8_t sX[2][kXTile * kXLd];
+  __shared__ uint32_t sR[kXTile * kXWords];
+  __shared__ __align__(16) int32_t sSum[kXTile];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1, lc = lane & 31, lh = lane >> 5;
+  const int j0 = (int)blockIdx.x * kXTile;
   const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-  const int tid = threadIdx.x;
-  const int pl = tid >> 2, cg = tid & 3;   // pattern in the pass, group of 16 columns
-  for (int q0 = p0; q0 < p1; q0 += kXRows) {
-    int32_t z[16];
+  const int ns = (k_raw + kXStage - 1) / kXStage, row_tiles = (n + kXTile - 1) / kXTile;
+  constexpr int kChunkStages = kXChunk / kXStage;
+
+  // R's bits of the inputs i0 .. i0 + kXChunk of every column: the Philox
+  // blocks that hold them, block b of column c at words 4b .. 4b + 3
+  auto draw = [&](int i0) {
+    const int len = min(kXChunk, k_raw - i0);
+    for (int t = tid; t < kXTile * kXBlocks; t += 256) {
+      const int c = t % kXTile, b = t / kXTile;
+      const uint64_t e = (uint64_t)(j0 + c) * (uint64_t)k_raw + (uint64_t)i0;
+      if (j0 + c >= k0 || b > (int)(((uint32_t)(e & 127) + (uint32_t)len - 1u) >> 7)) continue;
+      const U32x4 v = philox4x32_10((uint32_t)(e >> 7) + (uint32_t)b, 0xFFFFFFFFu, 0u, kStreamExpand, key0, key1);
+      uint32_t *d = sR + c * kXWords + 4 * b;
+      d[0] = v.x;
+      d[1] = v.y;
+      d[2] = v.z;
+      d[3] = v.w;
+    }
+  };
+
+  // a thread stages 64 bytes of one row: words 2 (tid & 1), + 1 of the stage
+  const int srow = tid >> 1, sbyte = 64 * (tid & 1);
+  for (int rt = (int)blockIdx.y; rt < row_tiles; rt += (int)gridDim.y) {
+    const int m0 = rt * kXTile;
+    const int8_t *xr = x + (size_t)min(m0 + srow, n - 1) * k_raw;   // rows past n repeat the last one
+    uint4 v[4];
+    int sum = 0;
+    auto load = [&](int st) {
+      const int i = st * kXStage + sbyte;
+      if (i + 64 <= k_raw) {
 #pragma unroll
-    for (int c = 0; c < 16; ++c) z[c] = 0;
-    const int mu = q0 + pl;
-    const int8_t *xr = x + (size_t)min(mu, n - 1) * k_raw;
-    for (int i0 = 0; i0 < k_raw; i0 += 32 * kXWords) {
-      const int nw = min(kXWords, (k_raw - i0 + 31) / 32);
-      __syncthreads();   // the previous pass's R words are no longer read
-      for (int t = tid; t < kXCols * nw; t += 256) {
-        const int c = t / nw, w = t % nw;
-        const int j = j0 + c, i = i0 + 32 * w;
-        uint32_t r = 0u;
-        if (j < k0) {
-          r = expand_bits32((uint64_t)j * (uint64_t)k_raw + (uint64_t)i, key0, key1);
-          const int valid = min(32, k_raw - i);   // past the row: no input, no weight
-          if (valid < 32) r &= (1u << valid) - 1u;
-        }
-        sR[c][w] = r;
-      }
-      __syncthreads();
-      for (int w = 0; w < nw; ++w) {
-        const int i = i0 + 32 * w;
-        // 32 inputs as 8 words of 4 int8 (zero past the row)
-        int xs[8];
+        for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], xr + i + 16 * q, 16);
+      } else {   // the row's end: zeros past it
 #pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          uint32_t v = 0u;
+        for (int q = 0; q < 4; ++q) {
+          uint32_t w[4] = {0u, 0u, 0u, 0u};
+          const int left = k_raw - (i + 16 * q);
+          if (left >= 16) {
+            __builtin_memcpy(w, xr + i + 16 * q, 16);
+          } else {
 #pragma unroll
-          for (int b = 0; b < 4; ++b) {
-            const int ii = i + 4 * q + b;
-            if (ii < k_raw) v |= (uint32_t)(uint8_t)xr[ii] << (8 * b);
+            for (int b = 0; b < 16; ++b)
+              if (b < left) w[b >> 2] |= (uint32_t)(uint8_t)xr[i + 16 * q + b] << (8 * (b & 3));
           }
-          xs[q] = (int)v;
+          v[q] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+      }
+    };
+    auto store = [&](uint8_t *d) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const uint4 a = v[2 * h], b = v[2 * h + 1];
+        const uint32_t d8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum = __builtin_amdgcn_sdot4((int)d8[q], 0x01010101, sum, false);
+        uint4 *o = reinterpret_cast<uint4 *>(d + srow * kXLd + sbyte + 32 * h);
+        o[0] = transpose4(d8[0], d8[2], d8[4], d8[6]);
+        o[1] = transpose4(d8[1], d8[3], d8[5], d8[7]);
+      }
+    };
+
+    v16i acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) acc[i][j] = (v16i){};
+    // the lane's columns: where their bits start in sR
+    int base[2];
+    uint32_t sh[2];
+    load(0);
+    for (int st = 0; st < ns; ++st) {
+      if (st % kChunkStages == 0) {
+        const int i0 = st * kXStage;
+        if (ns > kChunkStages || rt == (int)blockIdx.y) {
+          __syncthreads();   // the chunk before is no longer read
+          draw(i0);
         }
 #pragma unroll
-        for (int c = 0; c < 16; ++c) {
-          const uint32_t r = sR[cg * 16 + c][w];
+        for (int j = 0; j < 2; ++j) {
+          const int c = wn * 64 + j * 32 + lc;
+          const uint32_t off = (uint32_t)((uint64_t)(j0 + c) * (uint64_t)k_raw + (uint64_t)i0) & 127u;
+          base[j] = c * kXWords + (int)(off >> 5);
+          sh[j] = off & 31u;
+        }
+      }
+      store(sX[st & 1]);
+      __syncthreads();
+      if (st + 1 < ns) load(st + 1);
+      const uint8_t *t = sX[st & 1];
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            // the 4 weights of inputs 4q .. 4q + 3 as bytes +1 / -1 (0xFF);
-            // inputs past the row are 0, so their weight does not matter
-            // bit b of the nibble to bit 0 of byte b (the four shifted
-            // copies do not overlap), then 1 -> 0x01 and 0 -> 0xFF
-            const uint32_t nib = (r >> (4 * q)) & 0xFu;
-            const uint32_t spread = (nib * 0x00204081u) & 0x01010101u;
-            const uint32_t wv = ~(spread * 0xFEu);
-            z[c] = __builtin_amdgcn_sdot4(xs[q], (int)wv, z[c], false);
+      for (int ks = 0; ks < 2; ++ks) {
+        const int w = 2 * ks + lh;   // the lane's 32 inputs of the stage
+        uint4 a[2][2];
+        uint32_t r[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint4 *p = reinterpret_cast<const uint4 *>(t + (wm * 64 + i * 32 + lc) * kXLd + 32 * w);
+          a[i][0] = p[0];
+          a[i][1] = p[1];
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          const uint32_t *p = sR + base[j] + 4 * (st % kChunkStages) + w;
+          r[j] = __builtin_amdgcn_alignbit(p[1], p[0], sh[j]);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          v4i eb[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) eb[j][q] = (int)((r[j] >> (4 * h + q)) & 0x01010101u);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const v4i ea = {(int)a[i][h].x, (int)a[i][h].y, (int)a[i][h].z, (int)a[i][h].w};
+#pragma unroll
+            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ea, eb[j], acc[i][j], 0, 0, 0);
           }
         }
       }
     }
+    sum += __shfl_xor(sum, 1, 64);
+    if ((tid & 1) == 0) sSum[srow] = sum;
     __syncthreads();
+    // a_0 = (2 acc >= sum): result element e of lane l is row 8 (e >> 2) +
+    // 4 (l >> 5) + (e & 3), column l & 31; ballot k = 16 (2i + j) + e goes to
+    // lane k, which stores both rows' 32 bits
+    uint32_t blo = 0u, bhi = 0u;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) sZ[pl][cg * 16 + c] = z[c];
-    __syncthreads();
-    // a_0 = sign(z), sign(0) = +1: one ballot per (pattern, 64 columns)
-    const int wave = tid >> 6, lane = tid & 63;
-    for (int r = wave; r < kXRows; r += 4) {
-      const int m = q0 + r;
-      const bool pos = j0 + lane < k0 && sZ[r][lane] >= 0;
-      const uint64_t bal = __ballot(pos);
-      if (lane == 0 && m < p1) bits[(size_t)m * words_out + (j0 >> 6)] = bal;
+    for (int i = 0; i < 2; ++i) {
+      int4 s[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) s[q] = *reinterpret_cast<const int4 *>(&sSum[wm * 64 + i * 32 + 8 * q + 4 * lh]);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint64_t colok = __ballot(j0 + wn * 64 + j * 32 + lc < k0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          const int4 sq = s[e >> 2];
+          const int se = (e & 3) == 0 ? sq.x : (e & 3) == 1 ? sq.y : (e & 3) == 2 ? sq.z : sq.w;
+          const uint64_t bal = __ballot(2 * acc[i][j][e] >= se) & colok;
+          const uint32_t k = (uint32_t)((2 * i + j) * 16 + e);
+          blo = bmlp_input_writelane((uint32_t)bal, k, blo);
+          bhi = bmlp_input_writelane((uint32_t)(bal >> 32), k, bhi);
+        }
+      }
+    }
+    const int i = lane >> 5, j = (lane >> 4) & 1, e = lane & 15;
+    const int cw = ((j0 + wn * 64) >> 5) + j;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + (e & 3) + 4 * h;
+      if (m < n && cw < words32) bits[(size_t)m * words32 + cw] = h ? bhi : blo;
     }
   }
 }
@@ -329,10 +439,13 @@ hipError_t launch_binarize(const int8_t *x, int n, int K, const int8_t *thr, uin
 hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t seed, uint64_t *bits, hipStream_t s) {
   if (n <= 0 || k0 <= 0) return hipSuccess;
   if (k_raw <= 0) return hipErrorInvalidValue;
-  const int rows_per_block = 256;   // patterns per work-group (R made once per 256 patterns)
-  const dim3 grid((k0 + kXCols - 1) / kXCols, (n + rows_per_block - 1) / rows_per_block);
-  hipLaunchKernelGGL(expand_kernel, grid, dim3(256), 0, s, x, n, k_raw, k0, seed, rows_per_block, bits,
-                     (k0 + 63) / 64);
+  // Enough work-groups for two on each of 256 compute units and a half more
+  // (to even out the last ones); past that a work-group takes more row tiles
+  // and draws its columns' bits once for all of them.
+  const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n + kXTile - 1) / kXTile;
+  const dim3 grid(col_tiles, min(row_tiles, max(1, 768 / col_tiles)));
+  hipLaunchKernelGGL(expand_kernel, grid, dim3(256), 0, s, x, n, k_raw, k0, seed, reinterpret_cast<uint32_t *>(bits),
+                     2 * ((k0 + 63) / 64));
   return hipGetLastError();
 }
 

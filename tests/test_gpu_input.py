@@ -73,6 +73,25 @@ def test_expand(n, k_raw, k0):
     np.testing.assert_array_equal(bits.cpu().numpy().view(np.uint64), pack_np(want, bits.shape[1]))
 
 
+@pytest.mark.parametrize("n,k_raw,k0", [(1, 16, 64), (129, 128, 129), (127, 129, 65), (130, 1024, 200), (64, 1025, 128),
+                                        (3, 2177, 96), (520, 33, 32767)])
+def test_expand_edges(n, k_raw, k0):
+    """Stages, chunks of drawn bits and tiles with remainders, rows that
+    start at any byte, a work-group that walks two row tiles (the last
+    size), and rows of equal extreme features."""
+    torch = torch_cuda()
+    rng = np.random.default_rng(n + 3 * k_raw + k0)
+    x = _int8(rng, (n, k_raw))
+    x[0] = -128
+    x[n // 2] = 127
+    seed = 0x8000000180000001
+    note(f"expand edges n={n} k_raw={k_raw} k0={k0}")
+    bits = B.expand(torch.from_numpy(x).cuda(), k0, seed)
+    torch.cuda.synchronize()
+    want = ob.expand(x, ob.expansion_matrix(seed, k_raw, k0))
+    np.testing.assert_array_equal(bits.cpu().numpy().view(np.uint64), pack_np(want, bits.shape[1]))
+
+
 def test_training_on_expanded_inputs():
     torch = torch_cuda()
     p = Pair((256, 128), 5, 15, 64, 64, 0.25, seed=3)
