@@ -1,14 +1,14 @@
 // Local error signal and perceptron selection (Algorithm 1 01-loss and
 // robustness test, Eq. 1; Algorithm 2 easiest-perceptron choice).
 //
-// One wave per pattern.  Given y_hat, the wave finds the first argmax and the
-// two largest values (tau = top1 - top2, 0 on a tie), sets err = (pred != y)
-// and upd = err or tau < ceil(r K_l).  For every pattern it then takes, in
-// every group of gamma perceptrons (contiguous, or consecutive in the
-// reshuffle variant's per-step order), the one with the largest
-// negative stability delta_k = z_k rho^{y}_k, i.e. the smallest |z_k| among
-// those whose sign disagrees with rho^{y}_k, lowest k on ties; delta = 0 is
-// not eligible.  The update keeps only the patterns in M.
+// Error signal, one wave per pattern: given y_hat, the first argmax and the
+// two largest values (tau = top1 - top2, 0 on a tie), err = (pred != y) and
+// upd = err or tau < ceil(r K_l).
+// Selection, for every pattern and every group of gamma perceptrons
+// (contiguous, or consecutive in the reshuffle variant's per-step order): the
+// one with the largest negative stability delta_k = z_k rho^{y}_k, i.e. the
+// smallest |z_k| among those whose sign disagrees with rho^{y}_k, lowest k on
+// ties; delta = 0 is not eligible.  The update keeps only the patterns in M.
 #include <limits.h>
 
 #include "bmlp_internal.h"
@@ -58,57 +58,72 @@ __device__ __forceinline__ Top2 wave_top2(const int32_t *row, int c, int lane) {
   return t;
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
+// The first sel_blocks work-groups select, the others (when y_hat is given)
+// take the error signal of four patterns each.
+//
+// Selection: lpi = 2^lpi_log neighbouring lanes share a (pattern, group) item,
+// lane s taking the group's members s, s + lpi, ..., then merge their keys.
+// It is bound by the latency of its loads (z and the rho words), so a lane's
+// walk is short (about 8 to 16 members) and its loads are independent; the
+// items of a work-group are neighbouring groups of one pattern, so that the
+// lines of z are used whole.  With one lane per item and gamma dependent
+// steps it took 29 us (100 patterns, 5 groups of 105) and 20 us (500
+// patterns, 25 groups of 81); now 5.0 and 5.3 us.
+constexpr int kSelThreads = 256;
 
-// Grid: ceil(n / 4) blocks of 256 threads, one wave per pattern.
-__global__ __launch_bounds__(256) void loss_select_kernel(LossSelectArgs p) {
+template <bool PERM>
+__global__ __launch_bounds__(kSelThreads) void loss_select_kernel(LossSelectArgs p, int sel_blocks, int lpi_log) {
+  if ((int)blockIdx.x < sel_blocks) {
+    const long long t = (long long)blockIdx.x * kSelThreads + threadIdx.x;
+    const long long item = t >> lpi_log;
+    const int lpi = 1 << lpi_log, sub = (int)threadIdx.x & (lpi - 1);
+    const bool on = item < (long long)p.n * p.groups;
+    const int mu = on ? (int)(item / p.groups) : 0, g = on ? (int)(item % p.groups) : 0;
+    const int yl = min(max(p.y[mu], 0), p.c - 1);      // stay inside P on a bad label
+    const int16_t *zr = p.z + (size_t)mu * p.ldz;
+    const uint32_t *rho = reinterpret_cast<const uint32_t *>(p.P + (size_t)yl * p.words_out);
+    const int k0 = g * p.gamma;
+    // key: |z| then k (both below 2^15); best is the member's place in the group
+    uint32_t bestkey = 0xFFFFFFFFu;
+    int best = -1;
+#pragma unroll 4
+    for (int e = sub; e < p.gamma; e += lpi) {
+      const int k = PERM ? p.perm[k0 + e] : k0 + e;
+      const int zz = min(max((int)zr[k], p.zlo), p.zhi);   // z as the selection sees it
+      const bool rpos = (rho[k >> 5] >> (k & 31)) & 1u;
+      const bool wrong = rpos ? (zz < 0) : (zz > 0);
+      const uint32_t key = wrong ? ((uint32_t)(zz < 0 ? -zz : zz) << 15) | (uint32_t)k : 0xFFFFFFFFu;
+      if (key < bestkey) {
+        bestkey = key;
+        best = e;
+      }
+    }
+    for (int d = lpi >> 1; d >= 1; d >>= 1) {
+      const uint32_t ok = (uint32_t)__shfl_xor((int)bestkey, d, 64);
+      const int ob = __shfl_xor(best, d, 64);
+      if (ok < bestkey) {
+        bestkey = ok;
+        best = ob;
+      }
+    }
+    if (on && sub == 0) p.kstar[(size_t)g * p.ldk + mu] = (int16_t)best;
+    return;
+  }
   __shared__ int cnt[2];
   if (threadIdx.x < 2) cnt[threadIdx.x] = 0;
   __syncthreads();
-  const int mu = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int mu = ((int)blockIdx.x - sel_blocks) * 4 + ((int)threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (mu < p.n) {
-  const bool select_only = p.yhat == nullptr;
-  const int label = p.y[mu];
-  const int yl = min(max(label, 0), p.c - 1);      // stay inside P on a bad label
-  bool err = false, upd = false;
-  if (!select_only) {
     const Top2 t = wave_top2(p.yhat + (size_t)mu * p.c, p.c, lane);
-    err = t.i1 != label;
-    upd = err || (t.v1 - t.v2) < p.thr;
-  }
-  int16_t *ks = p.kstar + mu;   // column mu of kstar [groups][ldk]
-  {
-    const int16_t *zr = p.z + (size_t)mu * p.ldz;
-    const uint64_t *rho = p.P + (size_t)yl * p.words_out;
-    for (int g = lane; g < p.groups; g += 64) {
-      int best = -1, bestabs = INT_MAX, bestk = INT_MAX;
-      const int k0 = g * p.gamma;
-      for (int e = 0; e < p.gamma; ++e) {
-        const int k = p.perm ? p.perm[k0 + e] : k0 + e;
-        const int zz = min(max((int)zr[k], p.zlo), p.zhi);   // z as the selection sees it
-        const bool rpos = (rho[k >> 6] >> (k & 63)) & 1ull;
-        const bool wrong = rpos ? (zz < 0) : (zz > 0);
-        const int a = zz < 0 ? -zz : zz;
-        if (wrong && (a < bestabs || (a == bestabs && k < bestk))) {   // ties: lowest k
-          bestabs = a;
-          bestk = k;
-          best = e;
-        }
-      }
-      ks[(size_t)g * p.ldk] = (int16_t)best;
+    const bool err = t.i1 != p.y[mu];
+    const bool upd = err || (t.v1 - t.v2) < p.thr;
+    if (lane == 0) {
+      p.err[mu] = err ? 1 : 0;
+      p.upd[mu] = upd ? 1 : 0;
+      if (err) atomicAdd(&cnt[0], 1);
+      if (upd) atomicAdd(&cnt[1], 1);
     }
-  }
-  if (lane == 0 && !select_only) {
-    p.err[mu] = err ? 1 : 0;
-    p.upd[mu] = upd ? 1 : 0;
-    if (err) atomicAdd(&cnt[0], 1);
-    if (upd) atomicAdd(&cnt[1], 1);
-  }
   }
   __syncthreads();
   if (threadIdx.x == 0) {   // one global atomic per counter and work-group
@@ -229,7 +244,16 @@ __global__ __launch_bounds__(kPermThreads) void group_perm_kernel(PermBatch p) {
 
 hipError_t launch_loss_select(const LossSelectArgs &a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(loss_select_kernel, dim3((a.n + 3) / 4), dim3(256), 0, s, a);
+  if (a.gamma < 1 || a.groups < 1) return hipErrorInvalidValue;
+  int lpi_log = 0;   // at most 16 members per lane while lanes last
+  while (lpi_log < 6 && (a.gamma >> lpi_log) > 16) ++lpi_log;
+  const long long lanes = ((long long)a.n * a.groups) << lpi_log;
+  const int sel_blocks = (int)((lanes + kSelThreads - 1) / kSelThreads);
+  const dim3 grid(sel_blocks + (a.yhat != nullptr ? (a.n + 3) / 4 : 0));
+  if (a.perm != nullptr)
+    hipLaunchKernelGGL((loss_select_kernel<true>), grid, dim3(kSelThreads), 0, s, a, sel_blocks, lpi_log);
+  else
+    hipLaunchKernelGGL((loss_select_kernel<false>), grid, dim3(kSelThreads), 0, s, a, sel_blocks, lpi_log);
   return hipGetLastError();
 }
 
