@@ -86,6 +86,10 @@ struct FwdArgs {
   int pw_max, ystride;              // set by the launcher: last word of a P row; label stride
 };
 hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s);
+// The same for shapes with few tiles, and whether a shape is one (called by
+// launch_fwd_fp4 only).
+bool fwd_small_wins(const FwdArgs &a);
+hipError_t launch_fwd_small(const FwdArgs &a, hipStream_t s);
 
 // Classifier on the matrix cores, then the local error signal, for up to
 // kMaxClsLayers layers in one launch (ceil(n / 16) work-groups per layer),

@@ -54,6 +54,11 @@ __device__ __forceinline__ uint32_t class_bits_masked(uint32_t w, uint32_t valid
   if (s == 3) return fp4_sign_nibbles(w) & (((valid & 0x88888888u) >> 3) * 0xFu);
   return w & valid & (0x11111111u << s);
 }
+// the class-s operand of a word as ±1 in every class: the e2m1 sign bit from
+// bit 4t + s of each nibble, shifted to bit 3
+__device__ __forceinline__ uint32_t pm1_class(uint32_t w, int s) {
+  return fp4_sign_nibbles(s == 3 ? w : w << (3 - s));
+}
 // the E8M0 block scale of class s (exponent bias 127)
 __host__ __device__ constexpr int class_scale(int s) { return s == 0 ? 129 : s == 1 ? 128 : 127; }
 

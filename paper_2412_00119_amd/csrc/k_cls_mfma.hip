@@ -58,10 +58,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4;
 
-// the class-s operand of a pattern's words: ±1 from bit 4t + s of each word
-__device__ __forceinline__ uint32_t pm1_class(uint32_t w, int s) {
-  return fp4_sign_nibbles(s == 3 ? w : w << (3 - s));
-}
 __device__ __forceinline__ uint4 pm1_operand(const uint4 &w, int s) {
   return make_uint4(pm1_class(w.x, s), pm1_class(w.y, s), pm1_class(w.z, s), pm1_class(w.w, s));
 }

@@ -677,6 +677,7 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
     a.c = 1;
     a.pw_max = 0;
   }
+  if (fwd_small_wins(a)) return launch_fwd_small(a, s);
   const dim3 grid(a.nslices * a.nt_m * a.nt_n);
   const FwdSlice &s0 = a.sl[0];
 #define BMLP_FWD_ARGS s0.A, s0.B, a.y, s0.ld, s0.K, a.M, a.N, a.nt_m, a.nt_n, a.xcd_remap, a.ystride, a.mode, a
