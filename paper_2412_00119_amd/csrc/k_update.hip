@@ -27,10 +27,11 @@
 //   * h <- h + 2 sign(h) is u <- u +- 1 on the fired columns, one more planar
 //     addition, and W = sign(H) is u >= (B + 1) / 2.
 //
-// Work-group: (layer, group g, half of g's rows), 12 waves.  The group's selections U_l (each
-// pattern in M_l with a wrong perceptron in the group) are bucketed by
-// perceptron in LDS (counting sort), then the waves take the group's (row,
-// 2048-column chunk) items, lane l owning 32-column group chunk * 64 + l.  No
+// Work-group: (layer, group g, one of 2^split_log parts of g's rows), 12
+// waves.  The selections U_l of the part's rows (each pattern in M_l whose
+// wrong perceptron in the group is one of them) are bucketed by perceptron in
+// LDS (counting sort), then the waves take the part's (row, 2048-column
+// chunk) items, lane l owning 32-column group chunk * 64 + l.  No
 // two work-groups write the same bytes of H or W.
 #include "bmlp_internal.h"
 #include "philox.h"
@@ -38,13 +39,13 @@
 namespace bmlp {
 namespace {
 
-// Two work-groups of 12 waves per group of perceptrons, each taking half
-// of the group's rows: two of them fit a compute unit together (six waves
-// per SIMD), which hides more of the H loads behind the draws than one
-// work-group of 16 waves per compute unit did.
+// Work-groups of 12 waves: two of them fit a compute unit together (six
+// waves per SIMD), which hides more of the H loads behind the draws than one
+// work-group of 16 waves per compute unit did.  Each takes half of a group's
+// rows, or less where that leaves compute units idle (split_of).
 constexpr int kWaves = 12;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kSplit = 2;
+constexpr int kPerCu = 2;
 constexpr int kPre = 2;   // patterns per thread whose selection data the prologue loads up front
 constexpr int kPlanes = 15;   // counts up to 2^15 - 1 >= BMLP_MAX_BATCH
 
@@ -382,8 +383,8 @@ __device__ __host__ __forceinline__ int list_slots(int n, int gamma) { return ro
 // BMLP_STATS_STRIDE), so that |M_l| is requested before the argument
 // buffer has been read.
 template <int M, bool FULL>
-__global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
-    int nl, int b1, int b2, int b3, int b4, int b5, int b6, int b7, const int32_t *stats0, UpdateBatch p) {
+__global__ __launch_bounds__(kThreads, kPerCu * kWaves / 4) void update_kernel(
+    int nl, int split_log, int b1, int b2, int b3, int b4, int b5, int b6, int b7, const int32_t *stats0, UpdateBatch p) {
   extern __shared__ __align__(16) int smem[];
   __shared__ int wsum[kWaves];
   __shared__ int s_sel;
@@ -411,8 +412,10 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
   const int gamma = U.gamma, n = p.n, ldk = p.ldk;
   asm volatile("" ::"s"(mcount), "s"(upd), "s"(kstar), "s"(labels), "s"(gamma), "s"(n), "s"(ldk));
   const int block0 = li == 0 ? 0 : li == 1 ? b1 : li == 2 ? b2 : li == 3 ? b3 : li == 4 ? b4 : li == 5 ? b5 : li == 6 ? b6 : b7;
-  const int g = (bid - block0) / kSplit;
-  const int part = (bid - block0) % kSplit;
+  const int g = (bid - block0) >> split_log;
+  const int part = (bid - block0) & ((1 << split_log) - 1);
+  // this work-group's rows of the group
+  const int r_lo = (part * gamma) >> split_log, r_hi = ((part + 1) * gamma) >> split_log;
   const int16_t *kcol = kstar + (size_t)g * ldk;
   // The first kPre patterns of each thread: M_l flag, k* and label loaded
   // before |M_l| is known (in bounds: the index is clamped), so that they
@@ -438,20 +441,19 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
   if (tid == 0) s_sel = 0;
   for (int r = tid; r < gamma; r += kThreads) bucket[r] = 0;
   __syncthreads();
-  // U_l: the selections of the patterns in M_l
+  // U_l: the selections of the patterns in M_l (all are counted, those of
+  // this work-group's rows bucketed)
   int nsel = 0;
+  auto own_row = [&](int ks) { return ks >= r_lo && ks < r_hi; };
 #pragma unroll
-  for (int q = 0; q < kPre; ++q)
-    if (ks_pre[q] >= 0) {
-      atomicAdd(&bucket[ks_pre[q]], 1);
-      ++nsel;
-    }
+  for (int q = 0; q < kPre; ++q) {
+    nsel += ks_pre[q] >= 0;
+    if (own_row(ks_pre[q])) atomicAdd(&bucket[ks_pre[q]], 1);
+  }
   for (int mu = tid + kPre * kThreads; mu < n; mu += kThreads) {
     const int ks = upd[mu] ? kcol[mu] : -1;
-    if (ks >= 0) {
-      atomicAdd(&bucket[ks], 1);
-      ++nsel;
-    }
+    nsel += ks >= 0;
+    if (own_row(ks)) atomicAdd(&bucket[ks], 1);
   }
   nsel = wave_sum(nsel);
   if (lane == 0 && nsel) atomicAdd(&s_sel, nsel);
@@ -493,10 +495,10 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
     };
 #pragma unroll
     for (int q = 0; q < kPre; ++q)
-      if (ks_pre[q] >= 0) fill(tid + q * kThreads, ks_pre[q], y_pre[q]);
+      if (own_row(ks_pre[q])) fill(tid + q * kThreads, ks_pre[q], y_pre[q]);
     for (int mu = tid + kPre * kThreads; mu < p.n; mu += kThreads) {
       const int ks = U.upd[mu] ? kcol[mu] : -1;
-      if (ks >= 0) fill(mu, ks, p.y[mu]);
+      if (own_row(ks)) fill(mu, ks, p.y[mu]);
     }
   } else if (wave == 0) {
     // the same lists, each in pattern order: wave 0 walks the patterns 64
@@ -504,7 +506,8 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
     // lane order
     for (int base = 0; base < p.n; base += 64) {
       const int mu = base + lane;
-      const int ks = (mu < p.n && U.upd[mu]) ? kcol[mu] : -1;
+      const int sel = (mu < p.n && U.upd[mu]) ? kcol[mu] : -1;
+      const int ks = own_row(sel) ? sel : -1;
       uint32_t ent = 0u;
       if (ks >= 0) {
         const int k = U.perm ? U.perm[g * gamma + ks] : g * gamma + ks;
@@ -537,8 +540,6 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
 
   // work items: (row r, 2048-column chunk); lane l owns 32-column group
   // chunk * 64 + l of the row
-  // this work-group's rows: [r_lo, r_hi) of the group
-  const int r_lo = part * gamma / kSplit, r_hi = (part + 1) * gamma / kSplit;
   const int items = (r_hi - r_lo) * U.chunks;
   for (int it = wave; it < items; it += kWaves) {
     const int r = r_lo + it / U.chunks, chunk = it % U.chunks;
@@ -678,11 +679,26 @@ __global__ __launch_bounds__(kThreads, kSplit * kWaves / 4) void update_kernel(
   }
 }
 
+// log2 of the work-groups per group of perceptrons.  At least two; more while
+// a work-group still has more items (of the layer with the most) than waves
+// and the launch stays within two work-groups per compute unit, beyond
+// which it would only bucket each group's selections more often.  Measured,
+// two -> this many: 784 -> 256, 4 groups: 11.7 -> 7.4 us (8 work-groups);
+// 1000 -> 525 x 2, 10 groups of 105: 17.0 -> 8.0 (16); 784 -> 1024 x 2, 32
+// groups: 13.3 -> 8.8 (8); 3072 -> 2048 x 3, 96 groups: 23.9 -> 17.4 (4);
+// 1000 -> 2025 x 3, 75 groups of 81: 18.6 -> 16.5 (4), with 8 (600
+// work-groups, more than fit at once) 19.3.
+int split_of(int groups, int items) {
+  int s = 1;
+  while (s < 6 && (items >> s) > kWaves && ((long long)groups << (s + 1)) <= 512) ++s;
+  return s;
+}
+
 template <int M>
-void launch_planes(bool full, dim3 grid, dim3 block, size_t lds, hipStream_t s, const UpdateBatch &b) {
+void launch_planes(bool full, int split_log, dim3 grid, dim3 block, size_t lds, hipStream_t s, const UpdateBatch &b) {
   int b0[kMaxUpdLayers] = {};
   for (int i = 0; i < b.nl; ++i) b0[i] = b.L[i].block0;
-#define BMLP_UPD_ARGS b.nl, b0[1], b0[2], b0[3], b0[4], b0[5], b0[6], b0[7], b.L[0].stats, b
+#define BMLP_UPD_ARGS b.nl, split_log, b0[1], b0[2], b0[3], b0[4], b0[5], b0[6], b0[7], b.L[0].stats, b
   if (full)
     hipLaunchKernelGGL((update_kernel<M, true>), grid, block, lds, s, BMLP_UPD_ARGS);
   else
@@ -698,8 +714,7 @@ size_t update_lds_bytes(int gamma, int n) {
 
 hipError_t launch_update(UpdateBatch &b, hipStream_t s) {
   if (b.n <= 0 || b.nl <= 0) return hipSuccess;
-  int blocks = 0;
-  int gmax = 0;
+  int groups = 0, most = 0, gmax = 0;
   static_assert(kMaxUpdLayers == 8, "the kernel's leading arguments name layers 1..7");
   if (b.nl > kMaxUpdLayers) return hipErrorInvalidValue;
   for (int i = 0; i < b.nl; ++i) {
@@ -707,21 +722,27 @@ hipError_t launch_update(UpdateBatch &b, hipStream_t s) {
     // the kernel finds the stats row of layer i at stats0 + i * BMLP_STATS_STRIDE
     if (u.stats != b.L[0].stats + (size_t)i * BMLP_STATS_STRIDE) return hipErrorInvalidValue;
     u.chunks = (u.nw32 + 63) / 64;
-    u.block0 = blocks;
-    blocks += u.groups * kSplit;
+    groups += u.groups;
+    most = max(most, u.gamma * u.chunks);
     gmax = max(gmax, u.gamma);
+  }
+  const int split_log = split_of(groups, most);
+  int blocks = 0;
+  for (int i = 0; i < b.nl; ++i) {
+    b.L[i].block0 = blocks;
+    blocks += b.L[i].groups << split_log;
   }
   const dim3 grid(blocks), block(kThreads);
   const size_t lds = update_lds_bytes(gmax, b.n);
   const bool full = b.bound == (1 << h_planes(b.bound)) - 1;
   switch (h_planes(b.bound)) {
-    case 1: launch_planes<1>(full, grid, block, lds, s, b); break;
-    case 2: launch_planes<2>(full, grid, block, lds, s, b); break;
-    case 3: launch_planes<3>(full, grid, block, lds, s, b); break;
-    case 4: launch_planes<4>(full, grid, block, lds, s, b); break;
-    case 5: launch_planes<5>(full, grid, block, lds, s, b); break;
-    case 6: launch_planes<6>(full, grid, block, lds, s, b); break;
-    default: launch_planes<7>(full, grid, block, lds, s, b); break;
+    case 1: launch_planes<1>(full, split_log, grid, block, lds, s, b); break;
+    case 2: launch_planes<2>(full, split_log, grid, block, lds, s, b); break;
+    case 3: launch_planes<3>(full, split_log, grid, block, lds, s, b); break;
+    case 4: launch_planes<4>(full, split_log, grid, block, lds, s, b); break;
+    case 5: launch_planes<5>(full, split_log, grid, block, lds, s, b); break;
+    case 6: launch_planes<6>(full, split_log, grid, block, lds, s, b); break;
+    default: launch_planes<7>(full, split_log, grid, block, lds, s, b); break;
   }
   return hipGetLastError();
 }
