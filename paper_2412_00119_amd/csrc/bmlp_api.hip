@@ -434,6 +434,13 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
       }
     }
   }
+  // Where every group has at least 64 perceptrons and is contiguous, the
+  // forwards select: at 64 outright, above that in parts that the classifier
+  // launch merges.  The parts of all layers lie in the z scratch, which the
+  // other route (z stored, then a selection launch per layer) would need.
+  const bool parts = mfma && !reshuffle && select_parts_fit(p, n);
+  uint32_t *part = reinterpret_cast<uint32_t *>(ctx->ws + p.off_z);
+  const uint32_t *part_of[BMLP_MAX_LAYERS] = {};
   const uint64_t *a_prev = d_x;
   for (int l = 1; l <= p.L; ++l) {
     const LayerPlan &lp = p.layer[l - 1];
@@ -470,7 +477,12 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
       f.B = W; f.ldb = lp.words_in;
       f.M = n; f.N = lp.k_out; f.K = lp.k_in;
       f.abits = a; f.words_out = lp.words_out;
-      f.mode = fused ? kFwdFusedSelect : kFwdWriteZ;
+      f.mode = fused ? kFwdFusedSelect : parts ? kFwdSelectParts : kFwdWriteZ;
+      if (f.mode == kFwdSelectParts) {
+        f.part = part; f.gamma = lp.gamma;
+        part_of[l - 1] = part;
+        part += select_parts_words(lp, n);
+      }
       f.kstar = kstar; f.ldk = p.max_batch;
       f.y = d_y; f.c = p.c; f.P = P; f.ldp = lp.words_out;
       f.zlo = (float)zlo; f.zhi = (float)zhi;
@@ -479,7 +491,7 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
         f.zero = d_stats; f.nzero = BMLP_STATS_STRIDE * p.L;
       }
       BMLP_TIMED(ctx, BMLP_KERNEL_FWD, s, launch_fwd_fp4(f, s));
-      if (!fused) {   // Algorithm 2 from the stored z, before the next layer reuses it
+      if (f.mode == kFwdWriteZ) {   // Algorithm 2 from the stored z, before the next layer reuses it
         ls.yhat = nullptr;
         BMLP_TIMED(ctx, BMLP_KERNEL_SELECT, s, launch_loss_select(ls, s));
       }
@@ -511,7 +523,7 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
     // signal from it), loss and robustness test for every layer, one launch
     // per kMaxClsLayers layers
     ClsBatch cb{};
-    cb.n = n; cb.c = p.c; cb.y = d_y; cb.mode = kClsTrain; cb.ldy = p.ldy16;
+    cb.n = n; cb.c = p.c; cb.y = d_y; cb.mode = kClsTrain; cb.ldy = p.ldy16; cb.ldk = p.max_batch;
     for (int l = 1; l <= p.L; ++l) {
       const LayerPlan &lp = p.layer[l - 1];
       ClsLayer &c = cb.L[cb.nl++];
@@ -521,6 +533,7 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
       c.y16 = y16 + (size_t)(l - 1) * p.max_batch * p.ldy16;
       c.err = ctx->ws + lp.off_err; c.upd = ctx->ws + lp.off_upd;
       c.stats = d_stats + BMLP_STATS_STRIDE * (l - 1);
+      c.merge = SelectMerge{part_of[l - 1], reinterpret_cast<int16_t *>(ctx->ws + lp.off_kstar), lp.gamma, lp.groups};
       if (cb.nl == kMaxClsLayers || l == p.L) {
         BMLP_TIMED(ctx, BMLP_KERNEL_CLS, s, cls_gemm ? launch_cls_argmax(cb, s) : launch_cls_fp4(cb, s));
         cb.nl = 0;

@@ -56,7 +56,7 @@ hipError_t launch_cls_popcount(const uint64_t *a, int words, int k, const uint64
 // The same contraction gives the local classifier's y_hat = a_l P_l^T (A =
 // a_l, B = P_l) when the classes are too many for the classifier kernel
 // (kFwdWriteZ or kFwdWriteZ32, words_out = 0: no sign bits).
-enum { kFwdFusedSelect = 0, kFwdWriteZ = 1, kFwdPlain = 2, kFwdWriteZ32 = 3 };
+enum { kFwdFusedSelect = 0, kFwdWriteZ = 1, kFwdPlain = 2, kFwdWriteZ32 = 3, kFwdSelectParts = 4 };
 // One layer of a launch: its operands (A and B rows share the stride ld),
 // K and z.  A launch of several slices (kFwdWriteZ or kFwdWriteZ32 only)
 // runs the nt_m x nt_n tiles of each in turn; M, N and ldz are common.
@@ -74,11 +74,14 @@ struct FwdArgs {
   uint64_t *abits; int words_out;   // a_l bits [M][words_out]
   int mode;
   int16_t *kstar; int ldk;          // kFwdFusedSelect (gamma = 64): raw selection [groups][ldk]
-  const int32_t *y; int c;          // kFwdFusedSelect: labels [M] and class count
-  const uint64_t *P; int ldp;       // kFwdFusedSelect: P_l rows [c][ldp], rho^{y^mu} = P_l[y^mu]
+  uint32_t *part; int gamma;        // kFwdSelectParts (gamma > 64): selection keys (see SelectMerge)
+  // kFwdFusedSelect and kFwdSelectParts: labels [M] and class count, and P_l
+  // rows [c][ldp], rho^{y^mu} = P_l[y^mu]
+  const int32_t *y; int c;
+  const uint64_t *P; int ldp;
   int16_t *z; int ldz;              // kFwdWriteZ: z int16 [M][ldz]
   int32_t *z32;                     // kFwdWriteZ32: z int32 [M][ldz]
-  float zlo, zhi;                   // kFwdFusedSelect: the selection clips z to [zlo, zhi]
+  float zlo, zhi;                   // with a selection: it clips z to [zlo, zhi]
   int32_t *zero; int nzero;         // if set: zeroed by the first work-group (step statistics)
   int nslices;                      // > 1: sl[0 .. nslices) replace A, B, lda, ldb, K, z, z32
   FwdSlice sl[kMaxFwdSlices];       // (for one slice the launcher fills sl[0] from those fields)
@@ -98,6 +101,20 @@ hipError_t launch_fwd_small(const FwdArgs &a, hipStream_t s);
 // from it.
 constexpr int kClsMaxClasses = 128;
 enum { kClsTrain = 0, kClsYhatOnly = 1, kClsEval = 2 };
+// Contiguous groups of more than 64 perceptrons: a 64-column tile t of z holds
+// columns of at most two groups, floor(64 t / gamma) and the one after, and
+// the forward writes each pattern's best key within the tile of either one,
+// part [ceil(K_l / 64)][2][n] (the second only where it has columns in the
+// tile).  A key is below 2^27 for a wrong perceptron, then |z| << 8 (up to a
+// constant) | column of the tile, and at least 2^30 where the group has none
+// there.  The classifier launch that follows the forwards merges a group's
+// tiles in work-groups of its own, in order, so that equal |z| keep the
+// lowest column, and writes kstar.
+struct SelectMerge {
+  const uint32_t *part;             // null: nothing to merge
+  int16_t *kstar;                   // [groups][ldk]
+  int gamma, groups;
+};
 struct ClsLayer {
   const uint64_t *A;                // a_l bit rows [n][words]
   const uint64_t *P;                // P_l bit rows [c][words]
@@ -108,6 +125,7 @@ struct ClsLayer {
   int32_t *stats;                   // train: this layer's [4], adds [0] and [1]
   int32_t *correct;                 // eval: adds the correct count
   uint8_t *flag;                    // eval, if set: per pattern, 1 = correct, 2 = tau >= thr
+  SelectMerge merge;                // train: the selection left to merge
 };
 constexpr int kMaxClsLayers = 8;
 struct ClsBatch {
@@ -115,6 +133,7 @@ struct ClsBatch {
   int nl, n, c, mode;
   const int32_t *y;
   int ldy;                          // launch_cls_argmax: a multiple of 4, >= c
+  int ldk;                          // row stride of the merged kstar
 };
 hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s);
 // The local error signal (kClsTrain or kClsEval) from stored int16 y_hat rows.

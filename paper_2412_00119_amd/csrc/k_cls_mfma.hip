@@ -127,6 +127,42 @@ __device__ __forceinline__ Top2 dpp_top2(const Top2 &t) {
   return o;
 }
 
+// Merges item t of the launch's selections (see SelectMerge), layer by layer,
+// patterns fastest: the lowest key over the group's tiles in order.
+__device__ void merge_selection(const ClsBatch &p, long long t) {
+  for (int l = 0; l < p.nl; ++l) {
+    const SelectMerge &q = p.L[l].merge;
+    if (q.part == nullptr) continue;
+    const long long items = (long long)q.groups * p.n;
+    if (t >= items) {
+      t -= items;
+      continue;
+    }
+    const int g = (int)(t / p.n), mu = (int)(t % p.n);
+    const int k0 = g * q.gamma, k1 = k0 + q.gamma;
+    uint32_t best = 0xFFFFFFFFu;
+    int at = 0;
+    for (int tile = k0 >> 6; 64 * tile < k1; ++tile) {
+      // the group is the tile's second one where the tile starts before it
+      const uint32_t key = q.part[(size_t)(2 * tile + (64 * tile < k0 ? 1 : 0)) * p.n + mu];
+      if ((key >> 8) < (best >> 8)) {
+        best = key;
+        at = 64 * tile + (int)(key & 0x3Fu) - k0;
+      }
+    }
+    q.kstar[(size_t)g * p.ldk + mu] = best >= (1u << 27) ? (int16_t)-1 : (int16_t)at;
+    return;
+  }
+}
+
+// work-groups of `threads` threads that merge the batch's selections
+int merge_blocks(const ClsBatch &a, int threads) {
+  long long items = 0;
+  for (int l = 0; l < a.nl; ++l)
+    if (a.L[l].merge.part != nullptr) items += (long long)a.L[l].merge.groups * a.n;
+  return (int)((items + threads - 1) / threads);
+}
+
 template <int CB>
 struct ClsShape {
   static constexpr int KG = kWaves;              // wave groups along K (each wave takes every class block)
@@ -140,7 +176,7 @@ struct ClsShape {
 // preloaded into scalar registers when the wave starts, so that the layer
 // lookup and the label loads do not wait for a read of the argument buffer.
 template <int CB, bool ALIGNED, bool YHAT>
-__global__ __launch_bounds__(64 * kWaves) void cls_fp4_kernel(int pn, int pc, const int32_t *py, ClsBatch p) {
+__global__ __launch_bounds__(64 * kWaves) void cls_fp4_kernel(int pn, int pc, int pnl, const int32_t *py, ClsBatch p) {
   constexpr int KG = ClsShape<CB>::KG, CH = ClsShape<CB>::CH, LD = ClsShape<CB>::LD;
   __shared__ int red[KG][16][LD];        // y' partials of the K groups
   __shared__ int spa[KG][16];            // YHAT: P_a partials of the K groups
@@ -148,6 +184,12 @@ __global__ __launch_bounds__(64 * kWaves) void cls_fp4_kernel(int pn, int pc, co
 
   const int tid = threadIdx.x, kg = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int bpl = (pn + 15) / 16;               // work-groups per layer
+  if constexpr (!YHAT) {
+    if ((int)blockIdx.x >= pnl * bpl) {          // past the layers' work-groups
+      merge_selection(p, (long long)((int)blockIdx.x - pnl * bpl) * (64 * kWaves) + tid);
+      return;
+    }
+  }
   const ClsLayer &Lr = p.L[blockIdx.x / bpl];
   const int m0 = (blockIdx.x % bpl) * 16;
   const int lr = lane & 15, q = lane >> 4;       // row / class, and which 16 bytes of a super-block
@@ -333,6 +375,10 @@ __global__ __launch_bounds__(64 * kArgWaves) void cls_argmax_kernel(ClsBatch p) 
   __shared__ int cnt[3];   // block totals of err, upd, correct
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int bpl = (p.n + kArgWaves - 1) / kArgWaves;   // work-groups per layer
+  if ((int)blockIdx.x >= p.nl * bpl) {                 // past the layers' work-groups
+    merge_selection(p, (long long)((int)blockIdx.x - p.nl * bpl) * (64 * kArgWaves) + tid);
+    return;
+  }
   const ClsLayer &Lr = p.L[blockIdx.x / bpl];
   const int mu = (blockIdx.x % bpl) * kArgWaves + wave;
   if (tid < 3) cnt[tid] = 0;
@@ -403,14 +449,14 @@ void launch_cls_cb(const ClsBatch &a, bool aligned, bool yhat, dim3 grid, hipStr
   const dim3 block(64 * kWaves);
   if (aligned) {
     if (yhat)
-      hipLaunchKernelGGL((cls_fp4_kernel<CB, true, true>), grid, block, 0, s, a.n, a.c, a.y, a);
+      hipLaunchKernelGGL((cls_fp4_kernel<CB, true, true>), grid, block, 0, s, a.n, a.c, a.nl, a.y, a);
     else
-      hipLaunchKernelGGL((cls_fp4_kernel<CB, true, false>), grid, block, 0, s, a.n, a.c, a.y, a);
+      hipLaunchKernelGGL((cls_fp4_kernel<CB, true, false>), grid, block, 0, s, a.n, a.c, a.nl, a.y, a);
   } else {
     if (yhat)
-      hipLaunchKernelGGL((cls_fp4_kernel<CB, false, true>), grid, block, 0, s, a.n, a.c, a.y, a);
+      hipLaunchKernelGGL((cls_fp4_kernel<CB, false, true>), grid, block, 0, s, a.n, a.c, a.nl, a.y, a);
     else
-      hipLaunchKernelGGL((cls_fp4_kernel<CB, false, false>), grid, block, 0, s, a.n, a.c, a.y, a);
+      hipLaunchKernelGGL((cls_fp4_kernel<CB, false, false>), grid, block, 0, s, a.n, a.c, a.nl, a.y, a);
   }
 }
 
@@ -433,7 +479,7 @@ hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s) {
               (reinterpret_cast<uintptr_t>(L.P) & 15) == 0;
   }
   if (!yhat && a.y == nullptr) return hipErrorInvalidValue;
-  const dim3 grid(a.nl * ((a.n + 15) / 16));
+  const dim3 grid(a.nl * ((a.n + 15) / 16) + merge_blocks(a, 64 * kWaves));
   switch ((a.c + 15) / 16) {   // class blocks
     case 1: launch_cls_cb<1>(a, aligned, yhat, grid, s); break;
     case 2: launch_cls_cb<2>(a, aligned, yhat, grid, s); break;
@@ -454,7 +500,7 @@ hipError_t launch_cls_argmax(const ClsBatch &a, hipStream_t s) {
     return hipErrorInvalidValue;
   for (int l = 0; l < a.nl; ++l)
     if (a.L[l].y16 == nullptr || (reinterpret_cast<uintptr_t>(a.L[l].y16) & 7) != 0) return hipErrorInvalidValue;
-  const dim3 grid(a.nl * ((a.n + kArgWaves - 1) / kArgWaves)), block(64 * kArgWaves);
+  const dim3 grid(a.nl * ((a.n + kArgWaves - 1) / kArgWaves) + merge_blocks(a, 64 * kArgWaves)), block(64 * kArgWaves);
   hipLaunchKernelGGL(cls_argmax_kernel, grid, block, 0, s, a);
   return hipGetLastError();
 }

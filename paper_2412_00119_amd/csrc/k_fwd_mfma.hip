@@ -33,7 +33,10 @@
 //     columns k of the group with delta_k = z_k rho^{y}_k < 0, the smallest
 //     |z_k|, lowest k on ties (key = |z| << 8 | k, min-reduced across lanes
 //     with a butterfly reduce-scatter, so each lane ends with one row);
-//   * for any other gamma, z as int16 for the generic selection kernel;
+//   * for larger contiguous groups, the best key of each 64-column tile and
+//     group (at most two groups a tile), merged by the classifier launch;
+//   * for smaller or reshuffled groups, z as int16 for the generic selection
+//     kernel;
 //   * for the local classifier of a layer with many classes (A = a_l, B =
 //     P_l), y_hat as int16 or int32, and no sign bits.
 // Work-groups are mapped so that each XCD (work-group id mod 8) works on
@@ -228,7 +231,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // selection is not fused the launcher points them at valid memory).
   const int pr = tid >> 1, pw = tid & 1;
   const int pm = m0 + pr, pwg = (n0 >> 6) + pw;
-  const bool pvalid = pmode == kFwdFusedSelect && pm < pM && pwg < p.words_out;
+  const bool pvalid = (pmode == kFwdFusedSelect || pmode == kFwdSelectParts) && pm < pM && pwg < p.words_out;
 
   // Loads: a wave moves rows 32*wave .. 32*wave+31 of each operand.  Lane l
   // of instruction h fills LDS bytes UNIT*l of its kRowsPerDma rows: row
@@ -541,10 +544,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     }
   }
 
-  if (p.mode == kFwdFusedSelect) {
-    const int gcol0 = n0 + wn * 64;   // the wave's 64 columns are one group
+  if (p.mode == kFwdFusedSelect || p.mode == kFwdSelectParts) {
+    const int gcol0 = n0 + wn * 64;   // the wave's 64 columns
     if (gcol0 < p.N) {
-      const int g = gcol0 >> 6;
+      const int t = gcol0 >> 6;
       // Key of each of the lane's 32 rows q = 16*i + e over its 2 columns,
       // formed on the bits of the exact fp32 z: with s = -z where the
       // classifier weight is +1 and s = z where it is -1, perceptron k is
@@ -557,8 +560,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       uint32_t v[32];
       // z as the selection sees it: clipped only where [zlo, zhi] is
       // narrower than every |z| <= 32767 (the saturating variant)
-      auto keys = [&](auto clip_tag) {
+      auto keys = [&](auto clip_tag, auto part_tag, int lo, int hi) {
         constexpr bool kClip = decltype(clip_tag)::value;
+        // kPart: only columns [lo, hi) of the wave's 64 take part
+        constexpr bool kPart = decltype(part_tag)::value;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -572,14 +577,12 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
               const float zc = kClip ? fminf(fmaxf(acc[i][j][e], p.zlo), p.zhi) : acc[i][j][e];
               const float sz = __uint_as_float(__float_as_uint(zc) ^ (r & 0x80000000u));
               key[j] = __float_as_uint(sz) + ((uint32_t)(j * 32 + lc) - 0x3F800000u);
+              if constexpr (kPart) key[j] = j * 32 + lc >= lo && j * 32 + lc < hi ? key[j] : 0xFFFFFFFFu;
             }
             v[i * 16 + e] = min(key[0], key[1]);
           }
       };
-      if (p.zlo > -32767.f || p.zhi < 32767.f)
-        keys(std::true_type{});
-      else
-        keys(std::false_type{});
+      const bool clip = p.zlo > -32767.f || p.zhi < 32767.f;
       // Reduce-scatter over the 32 lanes of a half-wave: at each step a lane
       // keeps half of its rows (the upper half if the step's lane bit is
       // set) and takes the minimum with a partner's copy of those rows.
@@ -589,19 +592,40 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       // DPP row_mirror, row_half_mirror and two quad permutations, each of
       // which pairs a lane with one that differs in that bit.  Afterwards
       // lane lc holds the minimum over all 64 columns of row q = lc.
+      auto lowest = [&]() {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) {
-        const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 16], false, false);
-        v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
-      }
-      select_step<8, 0x140>(v, lc);   // row_mirror: lane i <-> 15 - i
-      select_step<4, 0x141>(v, lc);   // row_half_mirror: lane i <-> 7 - i
-      select_step<2, 0x4E>(v, lc);    // quad_perm [2,3,0,1]
-      select_step<1, 0xB1>(v, lc);    // quad_perm [1,0,3,2]
+        for (int k = 0; k < 16; ++k) {
+          const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 16], false, false);
+          v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
+        }
+        select_step<8, 0x140>(v, lc);   // row_mirror: lane i <-> 15 - i
+        select_step<4, 0x141>(v, lc);   // row_half_mirror: lane i <-> 7 - i
+        select_step<2, 0x4E>(v, lc);    // quad_perm [2,3,0,1]
+        select_step<1, 0xB1>(v, lc);    // quad_perm [1,0,3,2]
+        return v[0];
+      };
       const int i = lc >> 4, e = lc & 15;
       const int rl = wm * 64 + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
       const int m = m0 + rl;
-      if (m < p.M) p.kstar[(size_t)g * p.ldk + m] = (v[0] >= (1u << 27)) ? (int16_t)-1 : (int16_t)(v[0] & 0x3Fu);
+      if (p.mode == kFwdFusedSelect) {   // the wave's columns are one group
+        if (clip)
+          keys(std::true_type{}, std::false_type{}, 0, 64);
+        else
+          keys(std::false_type{}, std::false_type{}, 0, 64);
+        const uint32_t key = lowest();
+        if (m < p.M) p.kstar[(size_t)t * p.ldk + m] = key >= (1u << 27) ? (int16_t)-1 : (int16_t)(key & 0x3Fu);
+      } else {                           // columns [0, end) of one group, [end, 64) of the next
+        const int end = p.gamma - gcol0 % p.gamma, cols = min(64, p.N - gcol0);
+        for (int h = 0; h < (end < 64 ? 2 : 1); ++h) {
+          const int lo = h ? end : 0, hi = h ? cols : min(end, cols);
+          if (clip)
+            keys(std::true_type{}, std::true_type{}, lo, hi);
+          else
+            keys(std::false_type{}, std::true_type{}, lo, hi);
+          const uint32_t key = lowest();
+          if (m < p.M) p.part[(size_t)(2 * t + h) * p.M + m] = key;
+        }
+      }
     }
   } else if (p.mode == kFwdWriteZ || p.mode == kFwdWriteZ32) {
     const bool wide = p.mode == kFwdWriteZ32;
@@ -665,8 +689,9 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
     a.xcd_remap = 2;
   else
     a.xcd_remap = (a.nt_n % 8 == 0) ? 1 : 0;
-  if (a.mode == kFwdFusedSelect) {
+  if (a.mode == kFwdFusedSelect || a.mode == kFwdSelectParts) {
     if (a.y == nullptr || a.P == nullptr || a.c < 1) return hipErrorInvalidValue;
+    if (a.mode == kFwdSelectParts && (a.part == nullptr || a.gamma < 64)) return hipErrorInvalidValue;
     a.pw_max = a.words_out - 1;
     a.ystride = 1;
   } else {   // the label and rho loads read slice 0's A instead (always valid)

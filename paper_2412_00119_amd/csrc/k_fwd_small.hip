@@ -1,5 +1,5 @@
 // Hidden-layer forward (Algorithm 1: z = a_{l-1} W_l^T, a_l = sign(z), and
-// Algorithm 2's choice for gamma = 64) where the tiles of fwd_fp4_kernel are
+// Algorithm 2's choice for gamma >= 64) where the tiles of fwd_fp4_kernel are
 // too few to fill the chip.
 //
 // There a launch is bound by the latency of one work-group: first loads, K
@@ -104,7 +104,8 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_small_kernel(const uint64_t *
   // classifier word (64 columns of rho^{y}) is requested once it is here
   const int mq = m0 + RW * kg + min(lane, RW - 1);   // the lane's row in the epilogue
   int label = 0;
-  if (pmode == kFwdFusedSelect) label = py[min(mq, pM - 1)];
+  const bool selects = pmode == kFwdFusedSelect || pmode == kFwdSelectParts;
+  if (selects) label = py[min(mq, pM - 1)];
 
   const uint32_t rowbytes = 8u * (uint32_t)S.ld;
   const __amdgpu_buffer_rsrc_t rsA =
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_small_kernel(const uint64_t *
   // not used
 #pragma unroll
   for (int u = 0; u < CH; ++u) load(cur[u], kg + kWaves * u);
-  if (pmode == kFwdFusedSelect) {
+  if (selects) {
     const int yl = min(max(label, 0), p.c - 1);   // stay inside P on a bad label
     rho = p.P[(size_t)yl * p.ldp + min(n0 >> 6, p.pw_max)];
   }
@@ -213,44 +214,62 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_small_kernel(const uint64_t *
     }
     if (lane < RW && mq < pM) p.abits[(size_t)mq * p.words_out + (n0 >> 6)] = (uint64_t)lo | ((uint64_t)hi << 32);
   }
-  if (pmode == kFwdFusedSelect) {
+  if (selects) {
     // key of (row, column) as in fwd_fp4_kernel: bits(s) - bits(1.0f) + k with
     // s = -z where rho = +1, else z; below 2^27 exactly for the wrong
     // perceptrons, in the order (|z|, k)
     const uint32_t rlo = (uint32_t)rho, rhi = (uint32_t)(rho >> 32);
     const bool clip = p.zlo > -32767.f || p.zhi < 32767.f;
     const uint32_t kbase = (uint32_t)lane - 0x3F800000u;
-    uint32_t v[RW];
+    uint32_t keys[RW];
 #pragma unroll
     for (int q = 0; q < RW; ++q) {
       const uint64_t r = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)rlo, q) |
                          ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)rhi, q) << 32);
       const float zc = clip ? fminf(fmaxf(z[q], p.zlo), p.zhi) : z[q];
       const float s = __builtin_amdgcn_inverse_ballot_w64(r) ? -zc : zc;
-      v[q] = __float_as_uint(s) + kbase;
+      keys[q] = __float_as_uint(s) + kbase;
     }
     // minimum over the 64 lanes, the eight rows spread over them: lane bits
     // 5, 4 and 3 choose which of two rows a lane keeps, bits 2..0 just reduce
     static_assert(RW == 8, "three lane bits for the rows");
+    const int m = m0 + RW * kg + 4 * lh + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);   // the lane's row then
+    const bool writes = (lane & 7) == 0 && m < pM;
+    auto lowest = [&](uint32_t (&v)[RW]) {
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const auto sw = __builtin_amdgcn_permlane32_swap(v[k], v[k + 4], false, false);
-      v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
-    }
+      for (int k = 0; k < 4; ++k) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(v[k], v[k + 4], false, false);
+        v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
+      }
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 2], false, false);
-      v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
+      for (int k = 0; k < 2; ++k) {
+        const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 2], false, false);
+        v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
+      }
+      const bool up = (lane & 8) != 0;
+      const uint32_t send = up ? v[0] : v[1], keep = up ? v[1] : v[0];
+      uint32_t key = min(keep, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x140, 0xF, 0xF, false));   // row_mirror
+      key = dpp_min<0x141>(key);   // row_half_mirror
+      key = dpp_min<0x4E>(key);    // quad_perm [2,3,0,1]
+      return dpp_min<0xB1>(key);   // quad_perm [1,0,3,2]
+    };
+    if (pmode == kFwdFusedSelect) {   // the tile is a group
+      const uint32_t key = lowest(keys);
+      if (writes) p.kstar[(size_t)nt * p.ldk + m] = key >= (1u << 27) ? (int16_t)-1 : (int16_t)(key & 0x3Fu);
+    } else {                          // columns [0, end) of one group, [end, 64) of the next
+      const int end = p.gamma - n0 % p.gamma;
+      uint32_t v[RW];
+#pragma unroll
+      for (int q = 0; q < RW; ++q) v[q] = lane < end && col < pN ? keys[q] : 0xFFFFFFFFu;
+      uint32_t key = lowest(v);
+      if (writes) p.part[(size_t)(2 * nt) * pM + m] = key;
+      if (end < kCols) {
+#pragma unroll
+        for (int q = 0; q < RW; ++q) v[q] = lane >= end && col < pN ? keys[q] : 0xFFFFFFFFu;
+        key = lowest(v);
+        if (writes) p.part[(size_t)(2 * nt + 1) * pM + m] = key;
+      }
     }
-    const bool up = (lane & 8) != 0;
-    const uint32_t send = up ? v[0] : v[1], keep = up ? v[1] : v[0];
-    uint32_t key = min(keep, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)send, 0x140, 0xF, 0xF, false));   // row_mirror
-    key = dpp_min<0x141>(key);   // row_half_mirror
-    key = dpp_min<0x4E>(key);    // quad_perm [2,3,0,1]
-    key = dpp_min<0xB1>(key);    // quad_perm [1,0,3,2]
-    const int m = m0 + RW * kg + 4 * lh + 2 * ((lane >> 4) & 1) + ((lane >> 3) & 1);
-    if ((lane & 7) == 0 && m < pM)
-      p.kstar[(size_t)(n0 >> 6) * p.ldk + m] = key >= (1u << 27) ? (int16_t)-1 : (int16_t)(key & 0x3Fu);
   } else if (pmode != kFwdPlain && col < pN) {
 #pragma unroll
     for (int q = 0; q < RW; ++q) {

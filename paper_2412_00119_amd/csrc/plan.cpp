@@ -132,6 +132,16 @@ int z_bits(int k) {
   return b < 8 ? b : 8;
 }
 
+bool select_parts_fit(const Plan &p, int n) {
+  size_t words = 0;
+  for (int l = 1; l <= p.L; ++l) {
+    const LayerPlan &lp = p.layer[l - 1];
+    if (lp.gamma < 64) return false;
+    if (lp.gamma > 64) words += select_parts_words(lp, n);
+  }
+  return words * 4 <= (size_t)p.max_batch * p.ldz * 2;
+}
+
 size_t a_rows_offset(const Plan &p, int n, int l) {
   size_t o = 0;
   for (int j = 1; j < l; ++j) o = align256(o + (size_t)n * p.layer[j - 1].words_out * 8);

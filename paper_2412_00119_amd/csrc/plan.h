@@ -57,6 +57,14 @@ uint64_t reinforce_threshold(double p_r, int k);
 // min(8, ceil(log2(2 k))): the bits of z in the saturating variant.
 int z_bits(int k);
 
+// Selection keys of a layer for n patterns, in 32-bit words: two per pattern
+// and 64-column tile.
+inline size_t select_parts_words(const LayerPlan &lp, int n) { return (size_t)lp.words_out * 2 * n; }
+
+// Whether every layer's groups have at least 64 perceptrons and the keys of
+// the layers with more than 64 fit the z scratch together.
+bool select_parts_fit(const Plan &p, int n);
+
 // Byte offset of layer l's n activation rows when the rows of every layer
 // are packed one after another, each layer from a 256-byte boundary
 // (a_rows_offset(p, n, L + 1) is the total).

@@ -1,0 +1,37 @@
+"""Selection of contiguous groups of more than 64 perceptrons, whose keys the
+forwards write per 64-column tile and the classifier launch merges, against
+the oracle, bit for bit: group ends at every place of a tile, groups of many
+tiles, many ties of |z|, clipped z, both forward kernels, the launches for up
+to and for more than 128 classes, and networks whose keys do not fit the
+scratch (z is stored and selected from instead)."""
+import numpy as np
+import pytest
+
+from paper_2412_00119_amd import bmlp as B
+from paper_2412_00119_amd.synth import random_pm1
+
+from gpu_common import Pair, note
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("widths,gamma,c,n,variants", [
+    ((5, 130, 195), 65, 3, 40, 0),                      # |z| <= 5: ties across tiles
+    ((40, 254, 127), 127, 4, 33, 0),
+    ((200, 256, 128), 128, 5, 64, 0),
+    ((64, 1050, 525), 525, 6, 31, 0),                   # groups of nine tiles
+    ((333, 2025), 0, 140, 70, 0),                       # gamma* = 81, more than 128 classes
+    ((3000, 150, 75), 75, 7, 50, B.BMLP_VARIANT_SATURATE_Z),
+    ((1100, 2100), 105, 9, 600, 0),                     # the large-tile forward
+    ((1100, 2100), 105, 9, 600, B.BMLP_VARIANT_SATURATE_Z),
+    ((90,) + (96, 64, 81) * 3 + (75,), 0, 4, 20, 0),    # ten layers, some of 64
+    ((80,) + (75,) * 18, 0, 4, 20, 0),                  # keys of 18 layers: stored z
+])
+def test_select_parts(widths, gamma, c, n, variants):
+    rng = np.random.default_rng(sum(widths) + n)
+    p = Pair(widths, c, 15, n + 3, gamma, 0.25, seed=5, variants=variants)
+    for t in range(2):
+        note(f"parts {widths} gamma={gamma} variants={variants} step {t}")
+        x = random_pm1((n - 2 * t, widths[0]), rng)
+        y = rng.integers(0, c, n - 2 * t).astype(np.int32)
+        p.step(x, y, t, 0.5, tag=f"step {t}")
