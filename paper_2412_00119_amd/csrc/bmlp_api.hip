@@ -284,125 +284,10 @@ int setup(const bmlp_config *cfg, void *d_state, void *d_ws, void *stream, bmlp_
   return BMLP_OK;
 }
 
-}  // namespace
-}  // namespace bmlp
-
-using namespace bmlp;
-
-extern "C" {
-
-
-
-
-
-int bmlp_init(const bmlp_config *cfg, void *d_state, void *d_workspace, void *stream,
-              bmlp_ctx **out) {
-  return setup(cfg, d_state, d_workspace, stream, out, false);
-}
-
-int bmlp_attach(const bmlp_config *cfg, void *d_state, void *d_workspace, void *stream,
-                bmlp_ctx **out) {
-  return setup(cfg, d_state, d_workspace, stream, out, true);
-}
-
-int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void *stream) {
-  if (n < 0 || K < 1 || n > 65535) return BMLP_ESHAPE;
-  if (n > 0 && (d_pm1 == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_binarize(d_pm1, n, K, nullptr, d_bits, as_stream(stream)));
-  return BMLP_OK;
-}
-
-int bmlp_feature_median(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *stream) {
-  if (n < 1 || K < 1) return BMLP_ESHAPE;
-  if (d_x == nullptr || d_median == nullptr) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_feature_median(d_x, n, K, d_median, as_stream(stream)));
-  return BMLP_OK;
-}
-
-int bmlp_binarize(const int8_t *d_x, int32_t n, int32_t K, const int8_t *d_median, uint64_t *d_bits,
-                  void *stream) {
-  if (n < 0 || K < 1 || n > 65535) return BMLP_ESHAPE;
-  if (n > 0 && (d_x == nullptr || d_median == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_binarize(d_x, n, K, d_median, d_bits, as_stream(stream)));
-  return BMLP_OK;
-}
-
-int bmlp_expand(const int8_t *d_x, int32_t n, int32_t k_raw, int32_t k0, uint64_t seed, uint64_t *d_bits,
-                void *stream) {
-  if (n < 0 || k_raw < 1 || k_raw > BMLP_MAX_EXPAND_INPUTS || k0 < 1 || k0 > BMLP_MAX_WIDTH) return BMLP_ESHAPE;
-  if (n > 0 && (d_x == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_expand(d_x, n, k_raw, k0, seed, d_bits, as_stream(stream)));
-  return BMLP_OK;
-}
-
-int bmlp_forward(bmlp_ctx *ctx, const uint64_t *d_x, int32_t n, int32_t *d_yhat, void *stream) {
-  int st = check_ctx_batch(ctx, d_x, n);
-  if (st != BMLP_OK) return st;
-  if (n > 0 && d_yhat == nullptr) return BMLP_EINVAL;
-  if (n == 0) return BMLP_OK;
-  return forward_layers(ctx, d_x, n, as_stream(stream), d_yhat, nullptr, nullptr);
-}
-
-int bmlp_forward_noalloc(bmlp_ctx *ctx, const uint64_t *d_x, int32_t n, int32_t *d_yhat, void *stream) {
-  int st = check_ctx_batch(ctx, d_x, n);
-  if (st != BMLP_OK) return st;
-  if (n > 0 && d_yhat == nullptr) return BMLP_EINVAL;
-  if (n == 0) return BMLP_OK;
-  const Plan &p = ctx->plan;
-  const size_t need = a_rows_offset(p, n, p.L + 1);
-  if (need > (size_t)BMLP_NOALLOC_SCRATCH_BYTES) {
-    snprintf(g_last_error, sizeof(g_last_error),
-             "bmlp_forward_noalloc: %zu bytes of activation rows for n = %d exceed the static scratch of %zu bytes",
-             need, (int)n, (size_t)BMLP_NOALLOC_SCRATCH_BYTES);
-    return BMLP_ESHAPE;
-  }
-  uint8_t *base = nullptr;
-  {
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    if (ctx->device >= 0 && ctx->device < kMaxDevices) base = g_scratch_ptr[ctx->device];
-  }
-  if (base == nullptr) {   // not looked up at init: do it now, on the ctx's device
-    int cur = -1;
-    hipError_t e = hipGetDevice(&cur);
-    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
-    if (cur != ctx->device && (e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
-    st = scratch_setup(nullptr);
-    if (cur != ctx->device) (void)hipSetDevice(cur);
-    if (st != BMLP_OK) return st;
-    std::lock_guard<std::mutex> lock(g_scratch_mu);
-    base = g_scratch_ptr[ctx->device];
-  }
-  return forward_layers(ctx, d_x, n, as_stream(stream), d_yhat, nullptr, nullptr, 1, nullptr, base);
-}
-
-int bmlp_eval(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
-              int32_t *d_correct, void *stream) {
-  int st = check_ctx_batch(ctx, d_x, n);
-  if (st != BMLP_OK) return st;
-  if (n > 0 && (d_y == nullptr || d_correct == nullptr)) return BMLP_EINVAL;
-  if (n == 0) return BMLP_OK;
-  return forward_layers(ctx, d_x, n, as_stream(stream), nullptr, d_y, d_correct);
-}
-
-int bmlp_eval_exit(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
-                   int32_t *d_counts, void *stream) {
-  int st = check_ctx_batch(ctx, d_x, n);
-  if (st != BMLP_OK) return st;
-  if (n > 0 && (d_y == nullptr || d_counts == nullptr)) return BMLP_EINVAL;
-  if (n == 0) return BMLP_OK;
-  const Plan &p = ctx->plan;
-  hipStream_t s = as_stream(stream);
-  uint8_t *flags = ctx->ws + p.off_flag;
-  st = forward_layers(ctx, d_x, n, s, nullptr, d_y, d_counts, 3, flags);
-  if (st != BMLP_OK) return st;
-  BMLP_LAUNCH(launch_exit_count(flags, p.max_batch, p.L, n, d_counts, s));
-  return BMLP_OK;
-}
-
-
-
-int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
-                    uint64_t step, double p_r, int32_t *d_stats, void *stream) {
+// One training step.  next, if set: the batch of the following step, gathered
+// on the way (matrix-core path only).
+int train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n, uint64_t step, double p_r,
+               int32_t *d_stats, void *stream, const GatherArgs *next) {
   int st = check_ctx_batch(ctx, d_x, n);
   if (st != BMLP_OK) return st;
   if (d_stats == nullptr || (n > 0 && d_y == nullptr)) return BMLP_EINVAL;
@@ -524,6 +409,7 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
     // per kMaxClsLayers layers
     ClsBatch cb{};
     cb.n = n; cb.c = p.c; cb.y = d_y; cb.mode = kClsTrain; cb.ldy = p.ldy16; cb.ldk = p.max_batch;
+    if (next) cb.next = *next;
     for (int l = 1; l <= p.L; ++l) {
       const LayerPlan &lp = p.layer[l - 1];
       ClsLayer &c = cb.L[cb.nl++];
@@ -537,6 +423,7 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
       if (cb.nl == kMaxClsLayers || l == p.L) {
         BMLP_TIMED(ctx, BMLP_KERNEL_CLS, s, cls_gemm ? launch_cls_argmax(cb, s) : launch_cls_fp4(cb, s));
         cb.nl = 0;
+        cb.next.n = 0;   // gathered by the first launch
       }
     }
   }
@@ -572,6 +459,128 @@ int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int3
   return BMLP_OK;
 }
 
+}  // namespace
+}  // namespace bmlp
+
+using namespace bmlp;
+
+extern "C" {
+
+
+
+
+
+int bmlp_init(const bmlp_config *cfg, void *d_state, void *d_workspace, void *stream,
+              bmlp_ctx **out) {
+  return setup(cfg, d_state, d_workspace, stream, out, false);
+}
+
+int bmlp_attach(const bmlp_config *cfg, void *d_state, void *d_workspace, void *stream,
+                bmlp_ctx **out) {
+  return setup(cfg, d_state, d_workspace, stream, out, true);
+}
+
+int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void *stream) {
+  if (n < 0 || K < 1 || n > 65535) return BMLP_ESHAPE;
+  if (n > 0 && (d_pm1 == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
+  BMLP_LAUNCH(launch_binarize(d_pm1, n, K, nullptr, d_bits, as_stream(stream)));
+  return BMLP_OK;
+}
+
+int bmlp_feature_median(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *stream) {
+  if (n < 1 || K < 1) return BMLP_ESHAPE;
+  if (d_x == nullptr || d_median == nullptr) return BMLP_EINVAL;
+  BMLP_LAUNCH(launch_feature_median(d_x, n, K, d_median, as_stream(stream)));
+  return BMLP_OK;
+}
+
+int bmlp_binarize(const int8_t *d_x, int32_t n, int32_t K, const int8_t *d_median, uint64_t *d_bits,
+                  void *stream) {
+  if (n < 0 || K < 1 || n > 65535) return BMLP_ESHAPE;
+  if (n > 0 && (d_x == nullptr || d_median == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
+  BMLP_LAUNCH(launch_binarize(d_x, n, K, d_median, d_bits, as_stream(stream)));
+  return BMLP_OK;
+}
+
+int bmlp_expand(const int8_t *d_x, int32_t n, int32_t k_raw, int32_t k0, uint64_t seed, uint64_t *d_bits,
+                void *stream) {
+  if (n < 0 || k_raw < 1 || k_raw > BMLP_MAX_EXPAND_INPUTS || k0 < 1 || k0 > BMLP_MAX_WIDTH) return BMLP_ESHAPE;
+  if (n > 0 && (d_x == nullptr || d_bits == nullptr)) return BMLP_EINVAL;
+  BMLP_LAUNCH(launch_expand(d_x, n, k_raw, k0, seed, d_bits, as_stream(stream)));
+  return BMLP_OK;
+}
+
+int bmlp_forward(bmlp_ctx *ctx, const uint64_t *d_x, int32_t n, int32_t *d_yhat, void *stream) {
+  int st = check_ctx_batch(ctx, d_x, n);
+  if (st != BMLP_OK) return st;
+  if (n > 0 && d_yhat == nullptr) return BMLP_EINVAL;
+  if (n == 0) return BMLP_OK;
+  return forward_layers(ctx, d_x, n, as_stream(stream), d_yhat, nullptr, nullptr);
+}
+
+int bmlp_forward_noalloc(bmlp_ctx *ctx, const uint64_t *d_x, int32_t n, int32_t *d_yhat, void *stream) {
+  int st = check_ctx_batch(ctx, d_x, n);
+  if (st != BMLP_OK) return st;
+  if (n > 0 && d_yhat == nullptr) return BMLP_EINVAL;
+  if (n == 0) return BMLP_OK;
+  const Plan &p = ctx->plan;
+  const size_t need = a_rows_offset(p, n, p.L + 1);
+  if (need > (size_t)BMLP_NOALLOC_SCRATCH_BYTES) {
+    snprintf(g_last_error, sizeof(g_last_error),
+             "bmlp_forward_noalloc: %zu bytes of activation rows for n = %d exceed the static scratch of %zu bytes",
+             need, (int)n, (size_t)BMLP_NOALLOC_SCRATCH_BYTES);
+    return BMLP_ESHAPE;
+  }
+  uint8_t *base = nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (ctx->device >= 0 && ctx->device < kMaxDevices) base = g_scratch_ptr[ctx->device];
+  }
+  if (base == nullptr) {   // not looked up at init: do it now, on the ctx's device
+    int cur = -1;
+    hipError_t e = hipGetDevice(&cur);
+    if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
+    if (cur != ctx->device && (e = hipSetDevice(ctx->device)) != hipSuccess) return hip_fail(e, "hipSetDevice");
+    st = scratch_setup(nullptr);
+    if (cur != ctx->device) (void)hipSetDevice(cur);
+    if (st != BMLP_OK) return st;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    base = g_scratch_ptr[ctx->device];
+  }
+  return forward_layers(ctx, d_x, n, as_stream(stream), d_yhat, nullptr, nullptr, 1, nullptr, base);
+}
+
+int bmlp_eval(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
+              int32_t *d_correct, void *stream) {
+  int st = check_ctx_batch(ctx, d_x, n);
+  if (st != BMLP_OK) return st;
+  if (n > 0 && (d_y == nullptr || d_correct == nullptr)) return BMLP_EINVAL;
+  if (n == 0) return BMLP_OK;
+  return forward_layers(ctx, d_x, n, as_stream(stream), nullptr, d_y, d_correct);
+}
+
+int bmlp_eval_exit(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
+                   int32_t *d_counts, void *stream) {
+  int st = check_ctx_batch(ctx, d_x, n);
+  if (st != BMLP_OK) return st;
+  if (n > 0 && (d_y == nullptr || d_counts == nullptr)) return BMLP_EINVAL;
+  if (n == 0) return BMLP_OK;
+  const Plan &p = ctx->plan;
+  hipStream_t s = as_stream(stream);
+  uint8_t *flags = ctx->ws + p.off_flag;
+  st = forward_layers(ctx, d_x, n, s, nullptr, d_y, d_counts, 3, flags);
+  if (st != BMLP_OK) return st;
+  BMLP_LAUNCH(launch_exit_count(flags, p.max_batch, p.L, n, d_counts, s));
+  return BMLP_OK;
+}
+
+
+
+int bmlp_train_step(bmlp_ctx *ctx, const uint64_t *d_x, const int32_t *d_y, int32_t n,
+                    uint64_t step, double p_r, int32_t *d_stats, void *stream) {
+  return train_step(ctx, d_x, d_y, n, step, p_r, d_stats, stream, nullptr);
+}
+
 int bmlp_train_epoch(bmlp_ctx *ctx, const uint64_t *d_x_all, const int32_t *d_y_all, int32_t n_all,
                      const int32_t *d_order, int32_t n_order, int32_t batch, uint64_t step0, double p_r,
                      int32_t *d_stats, void *stream) {
@@ -584,17 +593,29 @@ int bmlp_train_epoch(bmlp_ctx *ctx, const uint64_t *d_x_all, const int32_t *d_y_
     return BMLP_EINVAL;
   if (reinterpret_cast<uintptr_t>(d_stats) & 7) return BMLP_EINVAL;
   hipStream_t s = as_stream(stream);
-  uint64_t *xb = reinterpret_cast<uint64_t *>(ctx->ws + p.off_xb);
-  int32_t *yb = reinterpret_cast<int32_t *>(ctx->ws + p.off_yb);
+  // Two batch buffers: while step b trains on one, the classifier launch of
+  // that step gathers batch b + 1 into the other (its last readers, the
+  // launches of step b - 1, are done by then).  The first batch, and every
+  // batch on the popcount path, is gathered by a launch of its own.
+  auto batch_of = [&](int b) {
+    GatherArgs g{};
+    g.x_all = d_x_all; g.y_all = d_y_all; g.n_all = n_all; g.words = p.layer[0].words_in;
+    g.order = d_order + (size_t)b * batch; g.n = batch;
+    g.xb = reinterpret_cast<uint64_t *>(ctx->ws + (b & 1 ? p.off_xb2 : p.off_xb));
+    g.yb = reinterpret_cast<int32_t *>(ctx->ws + (b & 1 ? p.off_yb2 : p.off_yb));
+    return g;
+  };
+  const bool ahead = use_mfma(p);
   for (int b = 0; b < nb; ++b) {
-    {
+    const GatherArgs g = batch_of(b);
+    if (b == 0 || !ahead) {
       ProfScope prof_scope{ctx};
-      BMLP_TIMED(ctx, BMLP_KERNEL_OTHER, s,
-                 launch_gather_batch(d_x_all, d_y_all, n_all, p.layer[0].words_in, d_order + (size_t)b * batch,
-                                     batch, xb, yb, s));
+      BMLP_TIMED(ctx, BMLP_KERNEL_OTHER, s, launch_gather_batch(g, s));
     }
-    const int st = bmlp_train_step(ctx, xb, yb, batch, step0 + (uint64_t)b, p_r,
-                                   d_stats + (size_t)b * BMLP_STATS_STRIDE * p.L, stream);
+    const GatherArgs following = batch_of(b + 1 < nb ? b + 1 : b);
+    const int st = train_step(ctx, g.xb, g.yb, batch, step0 + (uint64_t)b, p_r,
+                              d_stats + (size_t)b * BMLP_STATS_STRIDE * p.L, stream,
+                              ahead && b + 1 < nb ? &following : nullptr);
     if (st != BMLP_OK) return st;
   }
   return BMLP_OK;

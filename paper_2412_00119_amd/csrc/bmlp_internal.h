@@ -127,6 +127,16 @@ struct ClsLayer {
   uint8_t *flag;                    // eval, if set: per pattern, 1 = correct, 2 = tau >= thr
   SelectMerge merge;                // train: the selection left to merge
 };
+// A batch of a training set: xb[i] = x_all[order[i]], yb[i] = y_all[order[i]]
+// for i < n; indices outside [0, n_all) are clamped into it.
+struct GatherArgs {
+  const uint64_t *x_all;            // [n_all][words]
+  const int32_t *y_all;
+  const int32_t *order;
+  uint64_t *xb;                     // [n][words]
+  int32_t *yb;
+  int n_all, words, n;              // n = 0: nothing to gather
+};
 constexpr int kMaxClsLayers = 8;
 struct ClsBatch {
   ClsLayer L[kMaxClsLayers];
@@ -134,10 +144,12 @@ struct ClsBatch {
   const int32_t *y;
   int ldy;                          // launch_cls_argmax: a multiple of 4, >= c
   int ldk;                          // row stride of the merged kstar
+  GatherArgs next;                  // train: the next batch of an epoch, gathered by work-groups of the launch
+  int merge_blocks;                 // set by the launcher
 };
-hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s);
+hipError_t launch_cls_fp4(ClsBatch &a, hipStream_t s);
 // The local error signal (kClsTrain or kClsEval) from stored int16 y_hat rows.
-hipError_t launch_cls_argmax(const ClsBatch &a, hipStream_t s);
+hipError_t launch_cls_argmax(ClsBatch &a, hipStream_t s);
 
 // 01-loss, margin and M (when yhat is given), and the easiest wrong
 // perceptron of every group for every pattern (U_l is its restriction to the
@@ -164,10 +176,7 @@ hipError_t launch_eval_count(const int32_t *yhat, int c, const int32_t *y, int n
 // counts[l][1] += patterns whose first layer with flag & 2 (or the last
 // layer) is l, counts[l][2] += those of them with flag & 1.
 hipError_t launch_exit_count(const uint8_t *flags, int ldf, int L, int n, int32_t *counts, hipStream_t s);
-// Rows order[0..n) of a training set gathered into a batch: xb [n][words],
-// yb [n]; indices outside [0, n_all) are clamped into it.
-hipError_t launch_gather_batch(const uint64_t *x_all, const int32_t *y_all, int n_all, int words,
-                               const int32_t *order, int n, uint64_t *xb, int32_t *yb, hipStream_t s);
+hipError_t launch_gather_batch(const GatherArgs &a, hipStream_t s);
 
 // The input side (int8 features): per-feature lower median over n rows;
 // bit = (x >= thr) rows (thr null: 1 everywhere, i.e. x > 0, which packs ±1

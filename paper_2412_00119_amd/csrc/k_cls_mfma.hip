@@ -49,6 +49,7 @@
 
 #include "bmlp_internal.h"
 #include "fp4.h"
+#include "gather.h"
 
 namespace bmlp {
 namespace {
@@ -155,12 +156,23 @@ __device__ void merge_selection(const ClsBatch &p, long long t) {
   }
 }
 
-// work-groups of `threads` threads that merge the batch's selections
-int merge_blocks(const ClsBatch &a, int threads) {
+// What the work-groups past the layers' do, work-group b of them: the
+// selections left to merge, then the next batch's rows.  Neither depends on
+// the classifiers, and both run on compute units that those leave idle.
+__device__ __forceinline__ void side_work(const ClsBatch &p, int b, int threads, int tid) {
+  if (b < p.merge_blocks)
+    merge_selection(p, (long long)b * threads + tid);
+  else
+    gather_item(p.next, (uint32_t)(b - p.merge_blocks) * (uint32_t)threads + (uint32_t)tid);
+}
+
+// their number, for work-groups of `threads` threads
+int side_blocks(ClsBatch &a, int threads) {
   long long items = 0;
   for (int l = 0; l < a.nl; ++l)
     if (a.L[l].merge.part != nullptr) items += (long long)a.L[l].merge.groups * a.n;
-  return (int)((items + threads - 1) / threads);
+  a.merge_blocks = (int)((items + threads - 1) / threads);
+  return a.merge_blocks + (int)((gather_items(a.next) + threads - 1) / threads);
 }
 
 template <int CB>
@@ -186,7 +198,7 @@ __global__ __launch_bounds__(64 * kWaves) void cls_fp4_kernel(int pn, int pc, in
   const int bpl = (pn + 15) / 16;               // work-groups per layer
   if constexpr (!YHAT) {
     if ((int)blockIdx.x >= pnl * bpl) {          // past the layers' work-groups
-      merge_selection(p, (long long)((int)blockIdx.x - pnl * bpl) * (64 * kWaves) + tid);
+      side_work(p, (int)blockIdx.x - pnl * bpl, 64 * kWaves, tid);
       return;
     }
   }
@@ -376,7 +388,7 @@ __global__ __launch_bounds__(64 * kArgWaves) void cls_argmax_kernel(ClsBatch p) 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int bpl = (p.n + kArgWaves - 1) / kArgWaves;   // work-groups per layer
   if ((int)blockIdx.x >= p.nl * bpl) {                 // past the layers' work-groups
-    merge_selection(p, (long long)((int)blockIdx.x - p.nl * bpl) * (64 * kArgWaves) + tid);
+    side_work(p, (int)blockIdx.x - p.nl * bpl, 64 * kArgWaves, tid);
     return;
   }
   const ClsLayer &Lr = p.L[blockIdx.x / bpl];
@@ -462,7 +474,7 @@ void launch_cls_cb(const ClsBatch &a, bool aligned, bool yhat, dim3 grid, hipStr
 
 }  // namespace
 
-hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s) {
+hipError_t launch_cls_fp4(ClsBatch &a, hipStream_t s) {
   if (a.n <= 0 || a.nl <= 0) return hipSuccess;
   if (a.c < 1 || a.c > kClsMaxClasses || a.nl > kMaxClsLayers) return hipErrorInvalidValue;
   const bool yhat = a.mode == kClsYhatOnly;
@@ -479,7 +491,7 @@ hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s) {
               (reinterpret_cast<uintptr_t>(L.P) & 15) == 0;
   }
   if (!yhat && a.y == nullptr) return hipErrorInvalidValue;
-  const dim3 grid(a.nl * ((a.n + 15) / 16) + merge_blocks(a, 64 * kWaves));
+  const dim3 grid(a.nl * ((a.n + 15) / 16) + side_blocks(a, 64 * kWaves));
   switch ((a.c + 15) / 16) {   // class blocks
     case 1: launch_cls_cb<1>(a, aligned, yhat, grid, s); break;
     case 2: launch_cls_cb<2>(a, aligned, yhat, grid, s); break;
@@ -493,14 +505,14 @@ hipError_t launch_cls_fp4(const ClsBatch &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_cls_argmax(const ClsBatch &a, hipStream_t s) {
+hipError_t launch_cls_argmax(ClsBatch &a, hipStream_t s) {
   if (a.n <= 0 || a.nl <= 0) return hipSuccess;
   if (a.c < 1 || a.ldy < a.c || a.ldy % 4 != 0 || a.nl > kMaxClsLayers ||
       (a.mode != kClsTrain && a.mode != kClsEval))
     return hipErrorInvalidValue;
   for (int l = 0; l < a.nl; ++l)
     if (a.L[l].y16 == nullptr || (reinterpret_cast<uintptr_t>(a.L[l].y16) & 7) != 0) return hipErrorInvalidValue;
-  const dim3 grid(a.nl * ((a.n + kArgWaves - 1) / kArgWaves) + merge_blocks(a, 64 * kArgWaves)), block(64 * kArgWaves);
+  const dim3 grid(a.nl * ((a.n + kArgWaves - 1) / kArgWaves) + side_blocks(a, 64 * kArgWaves)), block(64 * kArgWaves);
   hipLaunchKernelGGL(cls_argmax_kernel, grid, block, 0, s, a);
   return hipGetLastError();
 }

@@ -12,6 +12,7 @@
 #include <limits.h>
 
 #include "bmlp_internal.h"
+#include "gather.h"
 #include "philox.h"
 
 namespace bmlp {
@@ -175,17 +176,8 @@ __global__ __launch_bounds__(256) void exit_count_kernel(const uint8_t *flags, i
   }
 }
 
-// one thread per 64-bit word of the batch; the word-0 thread of a row also
-// copies its label
-__global__ __launch_bounds__(256) void gather_batch_kernel(const uint64_t *x_all, const int32_t *y_all,
-                                                           int n_all, int words, const int32_t *order, int n,
-                                                           uint64_t *xb, int32_t *yb) {
-  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (t >= (long long)n * words) return;
-  const int i = (int)(t / words), w = (int)(t % words);
-  const int src = min(max(order[i], 0), n_all - 1);
-  xb[t] = x_all[(size_t)src * words + w];
-  if (w == 0) yb[i] = y_all[src];
+__global__ __launch_bounds__(256) void gather_batch_kernel(GatherArgs a) {
+  gather_item(a, blockIdx.x * 256u + threadIdx.x);
 }
 
 // The reshuffle variant's group order: perceptron k's key is word (k & 3)
@@ -283,13 +275,11 @@ hipError_t launch_exit_count(const uint8_t *flags, int ldf, int L, int n, int32_
   return hipGetLastError();
 }
 
-hipError_t launch_gather_batch(const uint64_t *x_all, const int32_t *y_all, int n_all, int words,
-                               const int32_t *order, int n, uint64_t *xb, int32_t *yb, hipStream_t s) {
-  const long long total = (long long)n * words;
+hipError_t launch_gather_batch(const GatherArgs &a, hipStream_t s) {
+  const long long total = gather_items(a);
   if (total <= 0) return hipSuccess;
-  if (n_all < 1) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(gather_batch_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, x_all, y_all,
-                     n_all, words, order, n, xb, yb);
+  if (a.n_all < 1) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(gather_batch_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

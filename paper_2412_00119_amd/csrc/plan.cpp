@@ -111,6 +111,10 @@ int make_plan(const bmlp_config *cfg, Plan *p) {
   p->off_yhat = wo;   // int32 [L][max_batch][c], or int16 [L][max_batch][ldy16]
   p->ldy16 = (p->c + 7) & ~7;
   wo = align256(wo + (size_t)p->L * nb * std::max((size_t)p->c * 4, (size_t)p->ldy16 * 2));
+  p->off_xb2 = wo;
+  wo = align256(wo + (size_t)nb * p->layer[0].words_in * 8);
+  p->off_yb2 = wo;
+  wo = align256(wo + (size_t)nb * 4);
   p->ws_bytes = wo;
   return BMLP_OK;
 }

@@ -38,6 +38,7 @@ struct Plan {
   size_t off_z, off_yhat;             // shared scratch in the workspace
   int ldy16;                          // y_hat as int16 rows [L][max_batch][ldy16] (in off_yhat)
   size_t off_flag, off_xb, off_yb;    // early-exit flags; a gathered batch (epoch driver)
+  size_t off_xb2, off_yb2;            // and the next one, gathered while a step runs
   size_t state_bytes, ws_bytes;
 };
 

@@ -64,6 +64,8 @@ static void check_layout(const bmlp_config &cfg, const Plan &p) {
   ws.push_back({p.off_flag, (size_t)p.L * nb});
   ws.push_back({p.off_xb, nb * p.layer[0].words_in * 8});
   ws.push_back({p.off_yb, nb * 4});
+  ws.push_back({p.off_xb2, nb * p.layer[0].words_in * 8});
+  ws.push_back({p.off_yb2, nb * 4});
   ws.push_back({p.off_z, nb * p.ldz * 2});
   ws.push_back({p.off_yhat, (size_t)p.L * nb * p.c * 4});
   for (auto *v : {&st, &ws}) {

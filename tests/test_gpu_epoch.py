@@ -142,3 +142,17 @@ def test_small_workload_five_epochs():
              f"{exits[:, 0].tolist()} of {len(te.y)}, exits {exits[:, 1].tolist()}")
         t += counts.shape[0]
         p_r = p_next
+
+
+@pytest.mark.parametrize("widths,c,gamma,n", [
+    ((70, 64), 130, 64, 100),             # more than 128 classes: the argmax launch gathers
+    ((333, 150, 75), 5, 75, 130),         # it merges selections too
+    ((90,) + (64,) * 9, 3, 64, 70),       # nine layers: the first of two classifier launches gathers
+    ((64, 64), 4, 64, 33),                # one batch: nothing to gather ahead
+])
+def test_batches_gathered_ahead(widths, c, gamma, n):
+    p = Pair(widths, c, 7, 32, gamma, 0.25, seed=2)
+    rng = np.random.default_rng(n)
+    x = np.where(rng.random((n, widths[0])) < 0.5, 1, -1).astype(np.int8)
+    y = rng.integers(0, c, n).astype(np.int32)
+    _epochs(p, x, y, 32, 2, 0.5, seed=7)
