@@ -16,11 +16,13 @@
 // per bit plane:
 //   * the count cnt_i of +1 contributions (x = a-word XOR [rho = -1]) of the
 //     S selectors of the row is accumulated bit-sliced (plane p = bit p of
-//     the 32 counters) with carry-save adder trees, the loads of a row's
-//     a-words issued sixteen at a time;
-//   * u + 2 cnt - S (= (h + dH + B) / 2) and the clip to [0, B] are
-//     ripple-carry additions and comparisons on the planes, wide enough to
-//     be exact;
+//     the 32 counters), sixteen words at a time through full adders whose
+//     running sums are the low planes themselves, with the loads of a batch
+//     issued together; the counters start at -ceil(S / 2), so that they end
+//     as d = cnt - ceil(S / 2);
+//   * u + 2 cnt - S = u + 2 d + (S odd) (= (h + dH + B) / 2) is one
+//     ripple-carry addition on the planes, wide enough to be exact, and the
+//     clip to [0, B] follows from its top planes;
 //   * the coarse reinforcement bytes arrive as bit planes (one Philox word
 //     per plane), so "u8 < T >> 24" is an 8-step bit-sliced comparison; the
 //     fine 24 bits are drawn only where u8 == T >> 24;
@@ -33,6 +35,8 @@
 // LDS (counting sort), then the waves take the part's (row, 2048-column
 // chunk) items, lane l owning 32-column group chunk * 64 + l.  No
 // two work-groups write the same bytes of H or W.
+#include <type_traits>
+
 #include "bmlp_internal.h"
 #include "philox.h"
 
@@ -47,7 +51,6 @@ constexpr int kWaves = 12;
 constexpr int kThreads = 64 * kWaves;
 constexpr int kPerCu = 2;
 constexpr int kPre = 2;   // patterns per thread whose selection data the prologue loads up front
-constexpr int kPlanes = 15;   // counts up to 2^15 - 1 >= BMLP_MAX_BATCH
 
 // A wave-uniform word the compiler must treat as unknown and keep in a
 // scalar register: bit-plane constants (0 or ~0) stay 32-bit operands of
@@ -68,79 +71,51 @@ __device__ __forceinline__ int wave_sum(int v) {
   return v;
 }
 
+__device__ __host__ __forceinline__ int round8(int v) { return (v + 7) & ~7; }
+
+// padding entry i of a row's selector list: pattern 0, signs alternating
+__device__ __forceinline__ uint16_t pad_entry(int i) { return (uint16_t)((i & 1) << 15); }
+
+// Three-input bitwise operations, one v_bitop3_b32 each.  (Written out, the
+// compiler shares a ^ b between the sum and the carry of a full adder and
+// needs four instructions for the two.)
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 __device__ __forceinline__ uint32_t maj(uint32_t a, uint32_t b, uint32_t c) {
-  return (a & b) | (c & (a ^ b));
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0xE8);
 }
 
-// Carry-save compression: a full adder turns three bit-vectors of one
-// weight into a sum of that weight and a carry of twice it (two 3-input
-// bitwise operations), a half adder does the same for two.
-__device__ __forceinline__ void fa(uint32_t a, uint32_t b, uint32_t c, uint32_t &s, uint32_t &cy) {
-  s = a ^ b ^ c;
-  cy = maj(a, b, c);
-}
-__device__ __forceinline__ void ha(uint32_t a, uint32_t b, uint32_t &s, uint32_t &cy) {
-  s = a ^ b;
-  cy = a & b;
+// Full adder on bit-vectors: a takes the sum of a, b and c, the carry (of
+// twice the weight) is returned.
+__device__ __forceinline__ uint32_t fa(uint32_t &a, uint32_t b, uint32_t c) {
+  const uint32_t cy = maj(a, b, c);
+  a = xor3(a, b, c);
+  return cy;
 }
 
-// Per lane, the number of set bits among x[0..8) as 4 planes n[0..4).
-__device__ __forceinline__ void compress8(const uint32_t (&x)[8], uint32_t (&n)[4]) {
-  uint32_t a, b, c, d, e, f, s1, c1, s2, c2, t, u;
-  fa(x[0], x[1], x[2], a, b);    // a:1 b:2
-  fa(x[3], x[4], x[5], c, d);    // c:1 d:2
-  fa(x[6], x[7], a, e, f);       // e:1 f:2
-  ha(c, e, n[0], s1);            // n0:1 s1:2
-  fa(b, d, f, s2, c1);           // s2:2 c1:4
-  ha(s2, s1, n[1], c2);          // n1:2 c2:4
-  ha(c1, c2, t, u);              // t:4 u:8
-  n[2] = t;
-  n[3] = u;
-}
-
-// Per lane, the number of set bits among x[0..16) as 5 planes n[0..5).
-__device__ __forceinline__ void compress16(const uint32_t (&x)[16], uint32_t (&n)[5]) {
-  // weight 1: 16 bits
-  uint32_t s[6], c2[8];
-  fa(x[0], x[1], x[2], s[0], c2[0]);
-  fa(x[3], x[4], x[5], s[1], c2[1]);
-  fa(x[6], x[7], x[8], s[2], c2[2]);
-  fa(x[9], x[10], x[11], s[3], c2[3]);
-  fa(x[12], x[13], x[14], s[4], c2[4]);
-  uint32_t t0, t1;
-  fa(s[0], s[1], s[2], t0, c2[5]);
-  fa(s[3], s[4], x[15], t1, c2[6]);
-  ha(t0, t1, n[0], c2[7]);
-  // weight 2: 8 bits
-  uint32_t w2a, w2b, w2c, c4[4];
-  fa(c2[0], c2[1], c2[2], w2a, c4[0]);
-  fa(c2[3], c2[4], c2[5], w2b, c4[1]);
-  fa(c2[6], c2[7], w2a, w2c, c4[2]);
-  ha(w2b, w2c, n[1], c4[3]);
-  // weight 4: 4 bits
-  uint32_t w4a, c8a, c8b;
-  fa(c4[0], c4[1], c4[2], w4a, c8a);
-  ha(w4a, c4[3], n[2], c8b);
-  // weight 8: 2 bits
-  ha(c8a, c8b, n[3], n[4]);
-}
-
-// c += n (n has NN planes), rippling the carry up to plane NP - 1.
-template <int NN, int NP>
-__device__ __forceinline__ void add_count(uint32_t (&c)[kPlanes], const uint32_t (&n)[NN]) {
-  uint32_t carry = 0u;
+// c += carry at plane FROM (mod 2^NP)
+template <int FROM, int NP>
+__device__ __forceinline__ void ripple(uint32_t (&c)[NP], uint32_t carry) {
 #pragma unroll
-  for (int p = 0; p < NP; ++p) {
-    if (p < NN) {
-      const uint32_t sum = c[p] ^ n[p] ^ carry;
-      carry = maj(c[p], n[p], carry);
-      c[p] = sum;
-    } else {
-      const uint32_t sum = c[p] ^ carry;
-      carry = c[p] & carry;
-      c[p] = sum;
-    }
+  for (int p = FROM; p < NP; ++p) {
+    const uint32_t t = c[p] & carry;
+    c[p] ^= carry;
+    carry = t;
   }
+}
+
+// c[0..3) += the set bits among x[0..8); returns the carry of weight 8
+// (planes from NP on do not exist: counters are mod 2^NP)
+template <int NP, int N>
+__device__ __forceinline__ uint32_t add8(uint32_t (&c)[NP], const uint32_t (&x)[N], int at) {
+  const uint32_t t0 = fa(c[0], x[at + 0], x[at + 1]), t1 = fa(c[0], x[at + 2], x[at + 3]);
+  const uint32_t t2 = fa(c[0], x[at + 4], x[at + 5]), t3 = fa(c[0], x[at + 6], x[at + 7]);
+  if constexpr (NP > 1) {
+    const uint32_t f0 = fa(c[1], t0, t1), f1 = fa(c[1], t2, t3);
+    if constexpr (NP > 2) return fa(c[2], f0, f1);
+  }
+  return 0u;
 }
 
 // The a_{l-1} rows are read through a buffer descriptor: the selector's row
@@ -167,104 +142,48 @@ __device__ __forceinline__ void read_entries16(const uint16_t *list, int i, uint
   e[7] = __builtin_amdgcn_readfirstlane(b.w);
 }
 
-// x[i] = a-word of entry i of e, flipped where rho = -1, for i < N; with
-// KEEP, entries i >= keep are zero (and read row 0, a valid address, since
-// the list slots past the row's selectors hold no entry).
-template <int N, bool KEEP>
-__device__ __forceinline__ void load_selectors(uint32_t (&x)[N], const uint32_t (&e)[8], int keep,
-                                               __amdgpu_buffer_rsrc_t rs, int rowbytes, int voff) {
+// x[i] = a-word of entry i of e, flipped where rho = -1, for i < N
+template <int N>
+__device__ __forceinline__ void load_selectors(uint32_t (&x)[N], const uint32_t (&e)[8], __amdgpu_buffer_rsrc_t rs,
+                                               int rowbytes, int voff) {
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const uint32_t ent = (e[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
-    const bool live = !KEEP || i < keep;
-    const int soff = live ? (int)(ent & 0x7FFFu) * rowbytes : 0;
     const uint32_t flip = (ent & 0x8000u) ? 0xFFFFFFFFu : 0u;
-    const uint32_t w = load_word(rs, voff, soff) ^ flip;
-    x[i] = live ? w : 0u;
+    x[i] = load_word(rs, voff, (int)(ent & 0x7FFFu) * rowbytes) ^ flip;
   }
 }
 
-// c += n (NN planes) where the counters are at most `bound` afterwards: the
-// carry ripples only through the planes in use (a uniform exit, so c stays
-// in place).
-template <int NN>
-__device__ __forceinline__ void add_count_upto(uint32_t (&c)[kPlanes], const uint32_t (&n)[NN], int bound) {
-  const int np = 32 - __clz(bound);
-  uint32_t carry = 0u;
-#pragma unroll
-  for (int p = 0; p < kPlanes; ++p) {
-    if (p < NN) {
-      const uint32_t sum = c[p] ^ n[p] ^ carry;
-      carry = maj(c[p], n[p], carry);
-      c[p] = sum;
-    } else {
-      if (p >= np) break;
-      const uint32_t sum = c[p] ^ carry;
-      carry = c[p] & carry;
-      c[p] = sum;
-    }
-  }
-}
-
-// Counts the +1 contributions of the row's S >= 1 selectors (list[beg ..
-// beg+S), beg a multiple of 8) into bit-sliced counters: batches of 16
-// through a carry-save tree, all 16 loads in flight together, each batch's
-// count added to the running one; the last batch (up to 15, or 8) masks
-// the slots past S.
-__device__ __forceinline__ void count_row(uint32_t (&c)[kPlanes], const uint16_t *list, int beg, int S,
+// d = cnt - ceil(S / 2) in NP planes (two's complement), cnt the +1
+// contributions of the row's S >= 1 selectors (list[beg .. beg + S), beg a
+// multiple of 8).  The list is filled up to a multiple of 8 with entries of
+// pattern 0 in alternating sign (pad_entry): a pair of them adds exactly one
+// to every column, which the start value takes off again, and the last one of
+// an odd number is masked out.  So no batch tests its entries one by one.
+template <int NP>
+__device__ __forceinline__ void count_row(uint32_t (&c)[NP], const uint16_t *list, int beg, int S,
                                           __amdgpu_buffer_rsrc_t rs, int rowbytes, int voff) {
+  const int pairs = (round8(S) - S) >> 1;
+  const uint32_t k0 = (uint32_t)(-((S + 1) >> 1) - pairs);
 #pragma unroll
-  for (int q = 0; q < kPlanes; ++q) c[q] = 0u;
+  for (int q = 0; q < NP; ++q) c[q] = plane_of(k0, q);
   int s0 = 0;
-  for (; s0 + 16 <= S; s0 += 16) {
-    uint32_t e[8], x[16], n[5];
+  for (; s0 + 8 < S; s0 += 16) {
+    uint32_t e[8], x[16];
     read_entries16(list, beg + s0, e);
-    load_selectors<16, false>(x, e, 16, rs, rowbytes, voff);
-    compress16(x, n);
-    if (s0 == 0) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q) c[q] = n[q];
-    } else {
-      add_count_upto<5>(c, n, s0 + 16);
-    }
+    load_selectors<16>(x, e, rs, rowbytes, voff);
+    const int left = S - s0;
+    x[15] = left < 16 && (left & 1) ? 0u : x[15];
+    const uint32_t g0 = add8(c, x, 0), g1 = add8(c, x, 8);
+    if constexpr (NP > 3) ripple<4>(c, fa(c[3], g0, g1));
   }
-  const int rem = S - s0;
-  if (rem == 0) return;
-  uint32_t e[8];
-  read_entries16(list, beg + s0, e);
-  if (rem <= 8) {
-    uint32_t x[8], n[4];
-    load_selectors<8, true>(x, e, rem, rs, rowbytes, voff);
-    compress8(x, n);
-    if (s0 == 0) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) c[q] = n[q];
-    } else {
-      add_count_upto<4>(c, n, S);
-    }
-  } else {
-    uint32_t x[16], n[5];
-    load_selectors<16, true>(x, e, rem, rs, rowbytes, voff);
-    compress16(x, n);
-    if (s0 == 0) {
-#pragma unroll
-      for (int q = 0; q < 5; ++q) c[q] = n[q];
-    } else {
-      add_count_upto<5>(c, n, S);
-    }
-  }
-}
-
-// x += k (mod 2^NB) for a constant k, bit-sliced.
-template <int NB>
-__device__ __forceinline__ void add_const(uint32_t (&x)[NB], uint32_t k) {
-  uint32_t carry = 0u;
-#pragma unroll
-  for (int p = 0; p < NB; ++p) {
-    const uint32_t kb = plane_of(k, p);
-    const uint32_t s = x[p] ^ kb ^ carry;
-    carry = maj(x[p], kb, carry);
-    x[p] = s;
+  if (s0 < S) {   // at most 8 left
+    uint32_t e[8], x[8];
+    read_entries16(list, beg + s0, e);
+    load_selectors<8>(x, e, rs, rowbytes, voff);
+    x[7] = ((S - s0) & 1) ? 0u : x[7];
+    const uint32_t g = add8(c, x, 0);
+    if constexpr (NP > 3) ripple<3>(c, g);
   }
 }
 
@@ -277,31 +196,47 @@ __device__ __forceinline__ uint32_t sign_of_sum(const uint32_t (&x)[NB], uint32_
   return x[NB - 1] ^ plane_of(k, NB - 1) ^ carry;
 }
 
-// u <- clip(u + 2 cnt - S, 0, B) on the M planes of u, computed in NB-bit
-// two's complement.  NB must hold z = u + 2 cnt - S, in [-S, B + S], and
-// z - (B + 1): 9 bits for S <= 63, 10 for S <= 255, 17 for S <= 16384
-// (B <= 127).
-template <int M, int NB>
-__device__ __forceinline__ void cp_apply(uint32_t (&u)[M], const uint32_t (&c)[kPlanes], int S, int B) {
-  // z = 2 cnt - S
-  uint32_t z[NB];
+// u <- clip(u + 2 cnt - S, 0, B) on the M planes of u where valid (elsewhere
+// 0, the padding's value), from the NP planes of d = cnt - ceil(S / 2).
+// z = u + 2 d + (S odd) in NP + 1 planes, two's complement, must hold
+// [-S, B + S]: NP = M + 1 for S <= 2^M, 9 for S <= 255, 16 for S <= 16384.
+template <int M, int NP, bool FULL>
+__device__ __forceinline__ void cp_apply(uint32_t (&u)[M], const uint32_t (&d)[NP], int S, int B, uint32_t valid) {
+  static_assert(NP > M, "z has planes above those of u");
+  uint32_t z[NP + 1];
+  const uint32_t odd = plane_of((uint32_t)S, 0);
+  z[0] = u[0] ^ odd;
+  uint32_t carry = u[0] & odd;
 #pragma unroll
-  for (int p = 0; p < NB; ++p) z[p] = (p >= 1 && p - 1 < kPlanes) ? c[p - 1] : 0u;
-  add_const<NB>(z, (uint32_t)(-S));
-  // z += u
-  uint32_t carry = 0u;
-#pragma unroll
-  for (int p = 0; p < NB; ++p) {
-    const uint32_t up = p < M ? u[p] : 0u;
-    const uint32_t t = z[p] ^ up ^ carry;
-    carry = maj(z[p], up, carry);
-    z[p] = t;
+  for (int p = 1; p <= NP; ++p) {
+    if (p < M) {
+      z[p] = xor3(u[p], d[p - 1], carry);
+      carry = maj(u[p], d[p - 1], carry);
+    } else {
+      z[p] = d[p - 1] ^ carry;
+      carry &= d[p - 1];
+    }
   }
-  // z > B  <=>  z - (B + 1) >= 0 ;  z < 0 is the sign plane
-  const uint32_t gt = ~sign_of_sum<NB>(z, (uint32_t)(-(B + 1)));
-  const uint32_t lt = z[NB - 1];
+  const uint32_t neg = z[NP];
+  uint32_t gt;   // z > B
+  if constexpr (FULL) {   // B = 2^M - 1: a plane from M on is set and z is not negative
+    gt = z[M];
 #pragma unroll
-  for (int p = 0; p < M; ++p) u[p] = (z[p] & ~(gt | lt)) | (plane_of((uint32_t)B, p) & gt);
+    for (int p = M + 1; p < NP; ++p) gt |= z[p];
+    gt &= ~neg;
+  } else {   // z - (B + 1) >= 0
+    gt = ~sign_of_sum<NP + 1>(z, (uint32_t)(-(B + 1)));
+  }
+  const uint32_t low = neg | ~valid, high = gt & valid;
+#pragma unroll
+  for (int p = 0; p < M; ++p) {
+    if constexpr (FULL) {
+      u[p] = (z[p] & ~low) | high;
+    } else {
+      const uint32_t v = z[p] & ~low;
+      u[p] = (plane_of((uint32_t)B, p) & high) | (v & ~high);
+    }
+  }
 }
 
 // Lanes where the M-plane value equals the constant v.
@@ -332,7 +267,7 @@ __device__ __forceinline__ void cp_sequential(uint32_t (&u)[M], const uint16_t *
     u[0] ^= g;
 #pragma unroll
     for (int q = 1; q < M; ++q) {
-      const uint32_t sum = u[q] ^ dec ^ carry;
+      const uint32_t sum = xor3(u[q], dec, carry);
       carry = maj(u[q], dec, carry);
       u[q] = sum;
     }
@@ -365,8 +300,6 @@ __device__ __forceinline__ uint32_t any_plane(const uint32_t (&u)[M]) {
   for (int q = 1; q < M; ++q) e |= u[q];
   return e;
 }
-
-__device__ __host__ __forceinline__ int round8(int v) { return (v + 7) & ~7; }
 
 // Selector list slots: every row's selectors padded to a multiple of 8, and
 // 16 more so that a batch read of 16 entries stays inside the list; a
@@ -481,6 +414,7 @@ __global__ __launch_bounds__(kThreads, kPerCu * kWaves / 4) void update_kernel(
     for (int r = b0; r < b1; ++r) {
       const int c = bucket[r];
       bucket[r] = run;
+      for (int i = c; i < round8(c); ++i) list[run + i] = pad_entry(i - c);
       run += round8(c);
     }
   }
@@ -564,29 +498,31 @@ __global__ __launch_bounds__(kThreads, kPerCu * kWaves / 4) void update_kernel(
     // ---- Clipped-Perceptron sum and clip ------------------------------------
     // the counts first, then the H planes (loaded after the counting, so
     // that they hold no registers during it)
-    const bool counted = S > 0 && !p.sequential;
-    uint32_t c[kPlanes];
-    if (counted) count_row(c, list, beg, S, rs, 4 * U.nw32, 4 * cwc);
     // plane p of the lane's group: word p * h_ps + cwc of the row
     uint32_t *urow = reinterpret_cast<uint32_t *>(U.H + (size_t)k * U.ld_h) + cwc;
     uint32_t u[M];
+    auto load_u = [&]() {
 #pragma unroll
-    for (int q = 0; q < M; ++q) u[q] = urow[(size_t)q * U.h_ps];
-    if (S > 0 && p.sequential) {
+      for (int q = 0; q < M; ++q) u[q] = urow[(size_t)q * U.h_ps];
+    };
+    auto cp_sum = [&](auto planes) {
+      constexpr int NP = decltype(planes)::value;
+      uint32_t c[NP];
+      count_row<NP>(c, list, beg, S, rs, 4 * U.nw32, 4 * cwc);
+      load_u();
+      cp_apply<M, NP, FULL>(u, c, S, Bi, validmask);
+    };
+    if (S == 0) {
+      load_u();
+    } else if (p.sequential) {
+      load_u();
       cp_sequential<M>(u, list, beg, S, Bi, validmask, U.a32, U.nw32, cwc);
-    } else if (counted) {
-      uint32_t un[M];
-#pragma unroll
-      for (int q = 0; q < M; ++q) un[q] = u[q];
-      if (S <= 63)
-        cp_apply<M, 9>(un, c, S, Bi);
-      else if (S <= 255)
-        cp_apply<M, 10>(un, c, S, Bi);
-      else
-        cp_apply<M, 17>(un, c, S, Bi);
-      // padding columns keep u = 0
-#pragma unroll
-      for (int q = 0; q < M; ++q) u[q] = (un[q] & validmask) | (u[q] & ~validmask);
+    } else if (S <= (1 << M)) {
+      cp_sum(std::integral_constant<int, M + 1>{});
+    } else if (S <= 255) {
+      cp_sum(std::integral_constant<int, 9>{});
+    } else {
+      cp_sum(std::integral_constant<int, 16>{});
     }
     // sign(h) after the Clipped-Perceptron step; reinforcement keeps it
     const uint32_t pos = FULL ? u[M - 1] : at_least<M>(u, (Bi + 1) >> 1);
@@ -648,7 +584,7 @@ __global__ __launch_bounds__(kThreads, kPerCu * kWaves / 4) void update_kernel(
       u[0] ^= gmask;
 #pragma unroll
       for (int q = 1; q < M; ++q) {
-        const uint32_t sum = u[q] ^ dn ^ carry;
+        const uint32_t sum = xor3(u[q], dn, carry);
         carry = maj(u[q], dn, carry);
         u[q] = sum;
       }
