@@ -331,6 +331,13 @@ class BMLP:
                 raise ValueError("state buffer does not match the configuration")
             self.state = state.to(self.device).contiguous().clone()
         self.ws = torch.empty(wb, dtype=torch.uint8, device=self.device)
+        # the per-call path: the raw handle of the current stream without a
+        # Stream object around it, the C functions, and the shapes that every
+        # call compares with
+        self._raw_stream = torch._C._cuda_getCurrentRawStream
+        self._lib = lib()
+        self._x_words = words64(self.widths[0])
+        self._stats_shape = torch.Size((self.n_layers, STATS_STRIDE))
         fn = bmlp_attach if state is not None else bmlp_init
         self.ctx = fn(self.cfg, self.state.data_ptr(), self.ws.data_ptr(), self._stream())
 
@@ -341,7 +348,7 @@ class BMLP:
             self.ctx = None
 
     def _stream(self) -> int:
-        return self.torch.cuda.current_stream(self.device).cuda_stream
+        return self._raw_stream(self.device.index)
 
     # ---- inputs -------------------------------------------------------------
     def pack(self, x_pm1):
@@ -357,12 +364,13 @@ class BMLP:
         torch = self.torch
         if x_bits.dtype != torch.int64 or x_bits.device != self.device or not x_bits.is_contiguous():
             raise ValueError("x must be a contiguous int64 bit-row tensor on the library's device")
-        if x_bits.dim() != 2 or x_bits.shape[1] != words64(self.widths[0]):
+        shape = x_bits.shape
+        if len(shape) != 2 or shape[1] != self._x_words:
             raise ValueError("x has the wrong number of words per row")
         if y is not None and (y.dtype != torch.int32 or y.device != self.device
-                              or not y.is_contiguous() or y.shape[0] != x_bits.shape[0]):
+                              or not y.is_contiguous() or y.shape[0] != shape[0]):
             raise ValueError("y must be a contiguous int32 tensor of n labels on the device")
-        return x_bits.shape[0]
+        return shape[0]
 
     # ---- the method -----------------------------------------------------------
     def train_step(self, x_bits, y, step: int, p_r: float, stats=None):
@@ -372,13 +380,12 @@ class BMLP:
         library fills (each layer's counts in a 128-byte row of their own)."""
         n = self._batch(x_bits, y)
         if stats is None:
-            stats = self.torch.empty((self.n_layers, STATS_STRIDE), dtype=self.torch.int32, device=self.device)
-        if tuple(stats.shape) != (self.n_layers, STATS_STRIDE) or stats.dtype != self.torch.int32 \
-                or not stats.is_contiguous():
+            stats = self.torch.empty(self._stats_shape, dtype=self.torch.int32, device=self.device)
+        if stats.shape != self._stats_shape or stats.dtype != self.torch.int32 or not stats.is_contiguous():
             raise ValueError(f"stats must be a contiguous int32 tensor [{self.n_layers}][{STATS_STRIDE}]")
-        bmlp_train_step(self.ctx, x_bits.data_ptr(), y.data_ptr(), n, int(step), float(p_r),
-                        stats.data_ptr(), self._stream())
-        return stats[:, :4]
+        _check(self._lib.bmlp_train_step(self.ctx, x_bits.data_ptr(), y.data_ptr(), n, int(step), float(p_r),
+                                         stats.data_ptr(), self._stream()), "bmlp_train_step")
+        return stats.narrow(1, 0, 4)
 
     def train_epoch(self, x_bits_all, y_all, order, step0: int, p_r: float, batch: Optional[int] = None):
         """One epoch (Algorithm 1's epoch loop) over the full batches of ``order``
@@ -419,7 +426,8 @@ class BMLP:
         n = self._batch(x_bits)
         out = self.torch.empty((self.n_layers, n, self.n_classes), dtype=self.torch.int32,
                                device=self.device)
-        bmlp_forward(self.ctx, x_bits.data_ptr(), n, out.data_ptr(), self._stream())
+        _check(self._lib.bmlp_forward(self.ctx, x_bits.data_ptr(), n, out.data_ptr(), self._stream()),
+               "bmlp_forward")
         return out
 
     def eval(self, x_bits, y, correct=None):
