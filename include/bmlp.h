@@ -215,6 +215,11 @@ int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void 
  * over the n >= 1 rows, the lower middle order statistic (element
  * floor((n-1)/2) of the sorted column), so the threshold is one of the
  * feature's values.
+ * bmlp_feature_median_split: the same with scratch memory of the caller's,
+ * 16-byte aligned and at least bmlp_feature_median_workspace_bytes(n, K)
+ * long (0 where the rows are few: d_ws may then be null), so that the rows
+ * are counted in parts and the whole chip counts.  It is free again when
+ * the call's work on the stream is done.
  * bmlp_binarize: median binarisation, bit = (x >= d_median[feature]).
  * 0 <= n <= 65535.
  * bmlp_expand: the fixed random ±1 expansion layer for integer inputs,
@@ -224,6 +229,9 @@ int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void 
  * 2^32 - 1, 0, 5), key = seed.  d_bits [n][words(k0)];
  * 1 <= k_raw <= BMLP_MAX_EXPAND_INPUTS, 1 <= k0 <= BMLP_MAX_WIDTH. */
 int bmlp_feature_median(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *stream);
+size_t bmlp_feature_median_workspace_bytes(int32_t n, int32_t K);
+int bmlp_feature_median_split(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *d_ws,
+                              size_t ws_bytes, void *stream);
 int bmlp_binarize(const int8_t *d_x, int32_t n, int32_t K, const int8_t *d_median, uint64_t *d_bits,
                   void *stream);
 int bmlp_expand(const int8_t *d_x, int32_t n, int32_t k_raw, int32_t k0, uint64_t seed, uint64_t *d_bits,

@@ -97,6 +97,8 @@ def lib() -> ctypes.CDLL:
             "bmlp_eval": (ctypes.c_int, [vp, vp, vp, i32, vp, vp]),
             "bmlp_eval_exit": (ctypes.c_int, [vp, vp, vp, i32, vp, vp]),
             "bmlp_feature_median": (ctypes.c_int, [vp, i32, i32, vp, vp]),
+            "bmlp_feature_median_workspace_bytes": (ctypes.c_size_t, [i32, i32]),
+            "bmlp_feature_median_split": (ctypes.c_int, [vp, i32, i32, vp, vp, ctypes.c_size_t, vp]),
             "bmlp_binarize": (ctypes.c_int, [vp, i32, i32, vp, vp, vp]),
             "bmlp_expand": (ctypes.c_int, [vp, i32, i32, i32, u64, vp, vp]),
             "bmlp_train_epoch": (ctypes.c_int, [vp, vp, vp, i32, vp, i32, i32, u64, dbl, vp, vp]),
@@ -207,6 +209,15 @@ def bmlp_feature_median(d_x: int, n: int, K: int, d_median: int, stream: int):
     _check(lib().bmlp_feature_median(d_x, n, K, d_median, stream), "bmlp_feature_median")
 
 
+def bmlp_feature_median_workspace_bytes(n: int, K: int) -> int:
+    return lib().bmlp_feature_median_workspace_bytes(n, K)
+
+
+def bmlp_feature_median_split(d_x: int, n: int, K: int, d_median: int, d_ws: int, ws_bytes: int, stream: int):
+    _check(lib().bmlp_feature_median_split(d_x, n, K, d_median, d_ws, ws_bytes, stream),
+           "bmlp_feature_median_split")
+
+
 def bmlp_binarize(d_x: int, n: int, K: int, d_median: int, d_bits: int, stream: int):
     _check(lib().bmlp_binarize(d_x, n, K, d_median, d_bits, stream), "bmlp_binarize")
 
@@ -220,7 +231,10 @@ def feature_median(x_int8):
     import torch
     n, K = x_int8.shape
     out = torch.empty(K, dtype=torch.int8, device=x_int8.device)
-    bmlp_feature_median(x_int8.data_ptr(), n, K, out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    wb = bmlp_feature_median_workspace_bytes(n, K)
+    ws = torch.empty(wb, dtype=torch.uint8, device=x_int8.device)
+    bmlp_feature_median_split(x_int8.data_ptr(), n, K, out.data_ptr(), ws.data_ptr(), wb,
+                              torch.cuda.current_stream().cuda_stream)
     return out
 
 

@@ -490,7 +490,22 @@ int bmlp_pack(const int8_t *d_pm1, int32_t n, int32_t K, uint64_t *d_bits, void 
 int bmlp_feature_median(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *stream) {
   if (n < 1 || K < 1) return BMLP_ESHAPE;
   if (d_x == nullptr || d_median == nullptr) return BMLP_EINVAL;
-  BMLP_LAUNCH(launch_feature_median(d_x, n, K, d_median, as_stream(stream)));
+  BMLP_LAUNCH(launch_feature_median(d_x, n, K, d_median, nullptr, as_stream(stream)));
+  return BMLP_OK;
+}
+
+size_t bmlp_feature_median_workspace_bytes(int32_t n, int32_t K) {
+  return n < 1 || K < 1 ? 0 : feature_median_ws_bytes(n, K);
+}
+
+int bmlp_feature_median_split(const int8_t *d_x, int32_t n, int32_t K, int8_t *d_median, void *d_ws,
+                              size_t ws_bytes, void *stream) {
+  if (n < 1 || K < 1) return BMLP_ESHAPE;
+  if (d_x == nullptr || d_median == nullptr) return BMLP_EINVAL;
+  const size_t need = feature_median_ws_bytes(n, K);
+  if (need > 0 && (d_ws == nullptr || ws_bytes < need)) return BMLP_EINVAL;
+  if (reinterpret_cast<uintptr_t>(d_ws) & 15) return BMLP_EINVAL;
+  BMLP_LAUNCH(launch_feature_median(d_x, n, K, d_median, need > 0 ? d_ws : nullptr, as_stream(stream)));
   return BMLP_OK;
 }
 

@@ -181,7 +181,9 @@ hipError_t launch_gather_batch(const GatherArgs &a, hipStream_t s);
 // The input side (int8 features): per-feature lower median over n rows;
 // bit = (x >= thr) rows (thr null: 1 everywhere, i.e. x > 0, which packs ±1
 // rows); the fixed random ±1 expansion layer sign(x R^T).
-hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, hipStream_t s);
+// ws, if set: feature_median_ws_bytes(n, K) bytes that the launches write and read.
+size_t feature_median_ws_bytes(int n, int K);
+hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, void *ws, hipStream_t s);
 hipError_t launch_binarize(const int8_t *x, int n, int K, const int8_t *thr, uint64_t *bits, hipStream_t s);
 hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t seed, uint64_t *bits, hipStream_t s);
 

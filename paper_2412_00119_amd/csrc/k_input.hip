@@ -14,118 +14,184 @@ namespace bmlp {
 namespace {
 
 constexpr int kStreamExpand = 5;
-// The median of kMedFeat neighbouring features per work-group, from 256-bin
-// histograms in LDS.
+// The median of F neighbouring features per work-group, from 256-bin
+// histograms in LDS, over the rows [split * rows, + rows) of the reference
+// set.  With one split the work-group takes the median itself; with several
+// (the caller gave scratch memory) it writes its counts, and
+// median_merge_kernel adds them up.
 //
-// What bounds it: each feature's whole column is counted by one work-group
-// (there is no scratch memory to merge partial counts in), so a compute unit
-// takes n cache lines, one per row, and the line fills (two cycles each)
-// are what is left.  To get there the counting must cost less than that:
-//   * a lane loads its row's kMedFeat bytes at once, and a thread has
-//     kMedRows rows in flight (16 waves: enough to cover memory latency);
-//   * the histograms are kept kMedCopies times, bin-major, one LDS bank per
-//     (copy, feature) slot, and lane l counts its bytes in the rotated order
-//     l, l + 1, ... (mod kMedFeat) into the copy l / kMedFeat.  So the 64
-//     lanes of every atomic are in 64 different banks, whatever the data
-//     (features with few distinct values included);
+// What bounds it: a work-group touches one cache line per row and F bytes, and
+// a compute unit fills a line in two cycles and adds to 64 LDS counters in
+// about eight.  So:
+//   * F = 16 where rows can be split, so that a line is touched half as often
+//     and every compute unit has rows to count; F = 8 where they cannot,
+//     since the features alone must fill the chip then;
+//   * a lane loads its row's F bytes at once, and a thread has kMedRows rows
+//     in flight (16 waves: enough to cover memory latency);
+//   * the histograms are kept 64 / F times, bin-major, one LDS bank per
+//     (copy, feature) slot, and at step j lane l counts its byte
+//     (l + j) mod 4 of dword (l / 4 + j / 4) mod F / 4 into the copy l / F.
+//     So the 64 lanes of every atomic are in 64 different banks, whatever the
+//     data (features with few distinct values included);
 //   * an atomic's address is one v_perm_b32: byte 0 the slot, byte 1 the
 //     value.
-// The work-groups of one XCD take neighbouring features, so a row's cache
-// line is fetched into one or two L2s instead of all eight.
-// 60000 x 784 (47 MB): 3810 -> 75 us (the kernel before had a work-group of
-// 256 threads per 64 features, one byte load per thread in flight).
-constexpr int kMedFeat = 8;
-constexpr int kMedCopies = 64 / kMedFeat;
+// The work-groups of one XCD take neighbouring features of the same rows, so
+// a row's cache line is fetched into one or two L2s instead of all eight.
+// 60000 x 784 (47 MB): 75.2 us in one part, 27.9 + 4.9 us (merge) in eight.
 constexpr int kMedThreads = 1024;
-constexpr int kMedRows = 8;      // rows per thread and pass
+constexpr int kMedRows = 4;      // rows per thread and pass
 
-// the 8 bytes at p (any alignment)
-__device__ __forceinline__ uint2 load8(const int8_t *p) {
-  uint2 v;
-  __builtin_memcpy(&v, p, 8);
-  return v;
+// where the features of a wave's lane l lie in running order: the value of
+// bins 4l .. 4l + 3 at which the count reaches floor((n - 1) / 2) + 1
+__device__ __forceinline__ void median_of_bins(const uint32_t (&c)[4], int n, int8_t *out) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t want = (uint32_t)((n - 1) / 2) + 1u;
+  const uint32_t own = c[0] + c[1] + c[2] + c[3];
+  uint32_t run = own;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t v = (uint32_t)__shfl_up((int)run, d, 64);
+    if (lane >= d) run += v;
+  }
+  uint32_t before = run - own;
+  if (before < want && run >= want) {
+    int v = 4 * lane;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      before += c[q];
+      if (before < want) ++v;
+      else break;
+    }
+    *out = (int8_t)(v - 128);
+  }
 }
 
+template <int F>
 __global__ __launch_bounds__(kMedThreads) void feature_median_kernel(const int8_t *__restrict__ x, int n, int K,
-                                                                     int8_t *__restrict__ med, int per_xcd) {
+                                                                     int8_t *__restrict__ med, int per_xcd,
+                                                                     int rows, uint4 *__restrict__ part) {
+  constexpr int kDw = F / 4, kCopies = 64 / F;
   __shared__ uint32_t hist[256][64];
   const int tid = threadIdx.x, lane = tid & 63;
-  // XCD b % 8 takes the tiles [per_xcd * (b % 8), + per_xcd)
-  const int tile = per_xcd * ((int)blockIdx.x & 7) + ((int)blockIdx.x >> 3);
+  // XCD b % 8 takes the tiles [per_xcd * (b % 8), + per_xcd), one split of
+  // the rows after the other, or (per_xcd 0) every eighth split of all tiles
+  const int xcd = (int)blockIdx.x & 7, idx = (int)blockIdx.x >> 3, tiles = (K + F - 1) / F;
+  const int split = per_xcd ? idx / per_xcd : 8 * (idx / tiles) + xcd;
+  const int tile = per_xcd ? per_xcd * xcd + idx % per_xcd : idx % tiles;
   // the last tile starts early enough to stay inside the row (its first
   // features are then counted twice, with the same result)
-  const int f0 = max(0, min(tile * kMedFeat, K - kMedFeat));
-  if (tile * kMedFeat >= K) return;
+  const int f0 = max(0, min(tile * F, K - F));
+  if (tile * F >= K) return;
   for (int i = tid; i < 256 * 64 / 4; i += kMedThreads) reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  const int rot = lane % kMedFeat, copy0 = lane - rot;
-  uint32_t slot[kMedFeat];   // byte address of the slot within a bin, per step
+  const int rot = lane % F, copy0 = lane - rot;
+  // byte addresses of the slots within a bin, four steps a dword; the perm
+  // selectors [slot byte j, value byte (rot + j) % 4, 0, 0] of step j
+  // (0x0C gives a zero byte, 0..3 the second source's bytes, 4..7 the first's)
+  uint32_t slots[kDw], sel[4];
 #pragma unroll
-  for (int j = 0; j < kMedFeat; ++j) slot[j] = 4u * (uint32_t)(copy0 + (rot + j) % kMedFeat);
+  for (int j = 0; j < F; ++j) {
+    const uint32_t f = 4u * (((uint32_t)rot / 4 + j / 4) % kDw) + ((uint32_t)rot + j) % 4;
+    const uint32_t byte = (4u * ((uint32_t)copy0 + f)) << (8 * (j & 3));
+    slots[j / 4] = (j & 3) ? slots[j / 4] | byte : byte;
+    if (j < 4) sel[j] = 0x0C0C0000u | ((4u + ((uint32_t)rot + j) % 4) << 8) | (uint32_t)j;
+  }
   uint8_t *const base = reinterpret_cast<uint8_t *>(hist);
-  auto count = [&](uint2 v) {
-    // value + 128 per byte, then the bytes rotated by rot
-    uint64_t w = ((uint64_t)(v.y ^ 0x80808080u) << 32) | (v.x ^ 0x80808080u);
-    if (rot) w = (w >> (8 * rot)) | (w << (64 - 8 * rot));
-    const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+  struct Row {
+    uint32_t d[kDw];
+  };
+  auto count = [&](Row v) {
+    // dword rot / 4 first
+    if constexpr (kDw == 4) {
+      const bool two = (rot & 8) != 0;
+      const uint32_t t[4] = {two ? v.d[2] : v.d[0], two ? v.d[3] : v.d[1], two ? v.d[0] : v.d[2], two ? v.d[1] : v.d[3]};
+      const bool one = (rot & 4) != 0;
 #pragma unroll
-    for (int j = 0; j < kMedFeat; ++j) {
-      // bytes: [slot, value, 0, 0] (selector 0x0C gives a zero byte, 0 the
-      // second source's byte 0, 4 + b the first source's byte b)
-      const uint32_t addr = __builtin_amdgcn_perm(j < 4 ? lo : hi, slot[j], 0x0C0C0000u | ((4u + (j & 3)) << 8));
-      atomicAdd(reinterpret_cast<uint32_t *>(base + addr), 1u);
+      for (int q = 0; q < 4; ++q) v.d[q] = one ? t[(q + 1) & 3] : t[q];
+    } else {
+      const bool one = (rot & 4) != 0;
+      const uint32_t a = v.d[0], b = v.d[1];
+      v.d[0] = one ? b : a;
+      v.d[1] = one ? a : b;
+    }
+#pragma unroll
+    for (int j = 0; j < F; ++j) {
+      // bin: the value + 128
+      const uint32_t w = v.d[j / 4] ^ 0x80808080u;
+      atomicAdd(reinterpret_cast<uint32_t *>(base + __builtin_amdgcn_perm(w, slots[j / 4], sel[j & 3])), 1u);
     }
   };
-  if (K >= kMedFeat) {
+  const uint32_t first = (uint32_t)split * (uint32_t)rows, end = min((uint32_t)n, first + (uint32_t)rows);
+  uint32_t r = first + (uint32_t)tid;
+  if (K >= F) {
     const int8_t *xf = x + f0;
-    const uint32_t rows = (uint32_t)n;
-    uint32_t r = (uint32_t)tid;
-    for (; r + (kMedRows - 1) * kMedThreads < rows; r += kMedRows * kMedThreads) {
-      uint2 v[kMedRows];
+    for (; r + (kMedRows - 1) * kMedThreads < end; r += kMedRows * kMedThreads) {
+      Row v[kMedRows];
 #pragma unroll
-      for (int q = 0; q < kMedRows; ++q) v[q] = load8(xf + (size_t)(r + q * kMedThreads) * K);
+      for (int q = 0; q < kMedRows; ++q) __builtin_memcpy(&v[q], xf + (size_t)(r + q * kMedThreads) * K, F);
 #pragma unroll
       for (int q = 0; q < kMedRows; ++q) count(v[q]);
     }
-    for (; r < rows; r += kMedThreads) count(load8(xf + (size_t)r * K));
+    for (; r < end; r += kMedThreads) {
+      Row v;
+      __builtin_memcpy(&v, xf + (size_t)r * K, F);
+      count(v);
+    }
   } else {   // rows of fewer bytes than a load
-    for (uint32_t r = (uint32_t)tid; r < (uint32_t)n; r += kMedThreads)
+    for (; r < end; r += kMedThreads)
       for (int f = 0; f < K; ++f) atomicAdd(&hist[(int)x[(size_t)r * K + f] + 128][copy0 + f], 1u);
   }
   __syncthreads();
-  // one wave per feature: lane l sums the copies of bins 4l .. 4l + 3, the
-  // wave scans, and the lane in whose bins the running count reaches
-  // floor((n - 1) / 2) + 1 writes the value
+  // one wave per feature: lane l sums the copies of bins 4l .. 4l + 3
   const int f = tid >> 6;
-  if (f < kMedFeat && f0 + f < K) {
-    const uint32_t want = (uint32_t)((n - 1) / 2) + 1u;
-    uint32_t c[4], own = 0u;
+  static_assert(F <= kMedThreads / 64, "a wave per feature");
+  if (f < F && f0 + f < K) {
+    uint32_t c[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       c[q] = 0u;
       // each lane starts at a copy of its own (spreads the banks)
 #pragma unroll
-      for (int k = 0; k < kMedCopies; ++k) c[q] += hist[4 * lane + q][((lane + k) % kMedCopies) * kMedFeat + f];
-      own += c[q];
+      for (int k = 0; k < kCopies; ++k) c[q] += hist[4 * lane + q][((lane + k) % kCopies) * F + f];
     }
-    uint32_t run = own;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const uint32_t v = (uint32_t)__shfl_up((int)run, d, 64);
-      if (lane >= d) run += v;
-    }
-    uint32_t before = run - own;
-    if (before < want && run >= want) {
-      int v = 4 * lane;
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        before += c[q];
-        if (before < want) ++v;
-        else break;
-      }
-      med[f0 + f] = (int8_t)(v - 128);
-    }
+    if (part == nullptr)
+      median_of_bins(c, n, med + f0 + f);
+    else   // the features that the last tile repeats are written twice, with the same counts
+      part[((size_t)split * K + f0 + f) * 64 + lane] = make_uint4(c[0], c[1], c[2], c[3]);
   }
+}
+
+// The splits' counts [splits][K][256] added up: a wave per feature, a lane
+// per four bins.
+__global__ __launch_bounds__(256) void median_merge_kernel(const uint4 *__restrict__ part, int splits, int n, int K,
+                                                           int8_t *__restrict__ med) {
+  const int f = (int)blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (f >= K) return;
+  uint32_t c[4] = {0u, 0u, 0u, 0u};
+#pragma unroll 8
+  for (int s = 0; s < splits; ++s) {
+    const uint4 v = part[((size_t)s * K + f) * 64 + lane];
+    c[0] += v.x;
+    c[1] += v.y;
+    c[2] += v.z;
+    c[3] += v.w;
+  }
+  median_of_bins(c, n, med + f);
+}
+
+constexpr int kMedFeatSplit = 16, kMedFeat = 8;
+
+inline int med_tiles(int K, int F) { return (K + F - 1) / F; }
+
+// Splits of the rows: about two work-groups for each of 256 compute units,
+// with at least one pass of rows each.  A multiple of 8 where the
+// tiles are too few to share out among the XCDs evenly: each XCD then has rows of
+// its own.  (60000 x 784: 8 splits 27.9 us, 16 34.8, 24 34.0, 32 40.9; 10 splits with
+// the tiles shared out 32.6, one of the XCDs idle.)
+int med_splits(int n, int K) {
+  const int tiles = med_tiles(K, kMedFeatSplit), most = (n - 1) / kMedThreads + 1;
+  if (tiles > 64 || most < 8) return min(max(1, 512 / tiles), most);
+  return 8 * min(64 / tiles, most / 8);
 }
 
 // Bit rows from int8 rows: bit = (x >= threshold of the column), the
@@ -415,10 +481,28 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
 
 }  // namespace
 
-hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, hipStream_t s) {
+size_t feature_median_ws_bytes(int n, int K) {
+  const int splits = med_splits(n, K);
+  return splits > 1 ? (size_t)splits * (size_t)K * 256 * sizeof(uint32_t) : 0;
+}
+
+hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, void *ws, hipStream_t s) {
   if (n <= 0 || K <= 0) return hipSuccess;
-  const int per_xcd = ((K + kMedFeat - 1) / kMedFeat + 7) / 8;   // tiles of each XCD
-  hipLaunchKernelGGL(feature_median_kernel, dim3(8 * per_xcd), dim3(kMedThreads), 0, s, x, n, K, med, per_xcd);
+  const int splits = ws != nullptr ? med_splits(n, K) : 1;
+  if (splits > 1) {
+    const int tiles = med_tiles(K, kMedFeatSplit), per_xcd = splits % 8 == 0 ? 0 : (tiles + 7) / 8;   // tiles of each XCD
+    const int rows = (n + splits - 1) / splits;
+    hipLaunchKernelGGL((feature_median_kernel<kMedFeatSplit>), dim3((per_xcd ? 8 * per_xcd : tiles) * splits), dim3(kMedThreads), 0, s, x, n,
+                       K, med, per_xcd, rows, static_cast<uint4 *>(ws));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(median_merge_kernel, dim3((K + 3) / 4), dim3(256), 0, s, static_cast<const uint4 *>(ws), splits, n,
+                       K, med);
+    return hipGetLastError();
+  }
+  const int per_xcd = (med_tiles(K, kMedFeat) + 7) / 8;
+  hipLaunchKernelGGL((feature_median_kernel<kMedFeat>), dim3(8 * per_xcd), dim3(kMedThreads), 0, s, x, n, K, med, per_xcd,
+                     n, static_cast<uint4 *>(nullptr));
   return hipGetLastError();
 }
 

@@ -59,6 +59,27 @@ def test_median_and_binarize_edges(n, k):
     np.testing.assert_array_equal(packed.cpu().numpy().view(np.uint64), pack_np(x, bits.shape[1]))
 
 
+@pytest.mark.parametrize("n,k", [(2048, 20), (2049, 16), (4097, 15), (6200, 31), (65000, 40), (5000, 4097), (9000, 129)])
+def test_median_split(n, k):
+    """Rows counted in one and in several parts (the last shorter than the
+    others), feature tiles that overlap at the end of a row, and the same
+    without scratch memory."""
+    torch = torch_cuda()
+    rng = np.random.default_rng(5 * n + k)
+    x = _int8(rng, (n, k))
+    x[:, 0] = np.where(np.arange(n) < (n + 1) // 2, 127, -128)
+    x[:, k - 1] = rng.integers(-1, 2, n)
+    note(f"median split n={n} k={k}")
+    xd = torch.from_numpy(x).cuda()
+    med = B.feature_median(xd)
+    alone = torch.empty_like(med)
+    B.bmlp_feature_median(xd.data_ptr(), n, k, alone.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    m = ob.feature_median(x)
+    np.testing.assert_array_equal(med.cpu().numpy(), m)
+    np.testing.assert_array_equal(alone.cpu().numpy(), m)
+
+
 @pytest.mark.parametrize("n,k_raw,k0", [(5, 1, 64), (300, 37, 100), (70, 300, 257), (257, 5000, 64),
                                         (64, 4096, 128)])
 def test_expand(n, k_raw, k0):
