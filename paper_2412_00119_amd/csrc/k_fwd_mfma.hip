@@ -17,7 +17,9 @@
 // other, so fewer VALU instructions per MFMA is a shorter K loop.
 //
 // A work-group computes a 128 x 128 tile of z (patterns x perceptrons) with
-// four waves of 64 x 64.  K is walked in steps of 512 elements (64 bytes of
+// four waves of 64 x 64, or, where such tiles would leave compute units idle
+// (half_rows), a 64 x 128 tile with four waves of 32 x 64 (FA, the 32-row A
+// fragments of a wave, 2 or 1: 6 operand instructions per MFMA instead of 4).  K is walked in steps of 512 elements (64 bytes of
 // each bit row) through a ring of kStages LDS buffers filled by
 // direct-to-LDS buffer loads (16 bytes per lane, or 4 where rows are not
 // 16-byte aligned) three steps ahead of the matrix cores, with one barrier
@@ -54,7 +56,7 @@ namespace {
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int TM = 128, TN = 128;   // tile of z
+constexpr int TN = 128;             // columns of a tile of z (64 FA rows)
 constexpr int KB = 64;              // bytes per row per K step (512 elements)
 constexpr int kStages = 4;          // LDS ring depth (kStages - 1 steps in flight)
 
@@ -147,9 +149,9 @@ __device__ __forceinline__ uint32_t bcnt_acc(uint32_t x, uint32_t acc) {
 
 // one reduce-scatter step at lane distance D, the partner given by DPP
 // control CTRL: rows k + D move into slot k on lanes with bit D set
-template <int D, int CTRL>
-__device__ __forceinline__ void select_step(uint32_t (&v)[32], int lc) {
-  const bool up = (lc & D) != 0;
+template <int D, int LANE, int CTRL, int N>
+__device__ __forceinline__ void select_step(uint32_t (&v)[N], int lc) {
+  const bool up = (lc & LANE) != 0;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     const uint32_t send = up ? v[k] : v[k + D];
@@ -167,7 +169,7 @@ __device__ __forceinline__ void select_step(uint32_t (&v)[32], int lc) {
 // the leading 16 dwords of a kernel's arguments are preloaded into scalar
 // registers when the wave starts (kernarg preloading), so the tile's first
 // loads do not wait for a read of the argument buffer.
-template <int UNIT, bool SLICED>
+template <int FA, int UNIT, bool SLICED>
 __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const uint64_t *pB, const int32_t *py, int pld,
                                                       int pK, int pM, int pN, int pnt_m, int pnt_n, int pxcd,
                                                       int pystride, int pmode, FwdArgs p) {
@@ -175,15 +177,19 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // names its array, so the compiler can tell a slot being read from the
   // slots the direct-to-LDS loads are still filling (it tells apart at most
   // eight such arrays).  66 KB in all: two work-groups fit on a CU.
+  constexpr int TM = 64 * FA;
   constexpr int kSlot = (TM + TN) * KB;
   __shared__ __align__(16) uint8_t s0[kSlot], s1[kSlot], s2[kSlot], s3[kSlot];
   __shared__ uint64_t sP[2][TM];       // rho^{y^mu} bits of the tile's 128 columns, per group
   __shared__ int32_t sY[TM];           // labels of the tile's rows
-  __shared__ uint32_t sPc[TM + TN];    // popcounts P_a (tile rows), then P_w (tile columns)
+  // popcounts P_a (tile rows; with FA = 1 the two waves of a row in turn),
+  // then P_w (tile columns)
+  __shared__ uint32_t sPc[128 + TN];
   static_assert(kStages == 4, "one named array per slot");
   constexpr int kRowsPerDma = 64 * UNIT / KB;     // rows per load instruction: 16 or 4
-  constexpr int kDma = 32 / kRowsPerDma;          // instructions per operand per wave and step
-  constexpr int kIssue = 2 * kDma;                // loads per wave and step
+  constexpr int kDmaA = 16 * FA / kRowsPerDma;    // instructions per wave and step, for each operand
+  constexpr int kDmaB = 32 / kRowsPerDma;
+  constexpr int kIssue = kDmaA + kDmaB;           // loads per wave and step
   static_assert(kIssue * (kStages - 2) < 64, "vmcnt range");
 
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -229,13 +235,13 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // the word of P_l is loaded once they have landed, to be used after the
   // K loop.  Both loads are unconditional (indices clamped; when the
   // selection is not fused the launcher points them at valid memory).
-  const int pr = tid >> 1, pw = tid & 1;
+  const int pr = (tid >> 1) & (TM - 1), pw = tid & 1;   // (FA = 1: each row twice)
   const int pm = m0 + pr, pwg = (n0 >> 6) + pw;
   const bool pvalid = (pmode == kFwdFusedSelect || pmode == kFwdSelectParts) && pm < pM && pwg < p.words_out;
 
-  // Loads: a wave moves rows 32*wave .. 32*wave+31 of each operand.  Lane l
+  // Loads: a wave moves a quarter of each operand's rows.  Lane l
   // of instruction h fills LDS bytes UNIT*l of its kRowsPerDma rows: row
-  // r = 32*wave + kRowsPerDma*h + (UNIT*l) / 64, physical 16-byte unit u,
+  // r = kRowsPerDma * (kDma*wave + h) + (UNIT*l) / 64, physical 16-byte unit u,
   // which holds logical unit u ^ swz(r) of that row (the XOR swizzle keeps
   // the operand reads conflict-free).  Rows past the matrix are clamped to
   // its last row.  A source past the end of its row (only in the last step)
@@ -243,16 +249,20 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // masks out, or, past the matrix, zeros: the loads go through buffer
   // descriptors sized to the matrices, so that a step costs one add per
   // load and no clamp.
-  uint32_t voffA[kDma], voffB[kDma];
+  uint32_t voffA[kDmaA], voffB[kDmaB];
   const uint32_t rowbytes = 8u * (uint32_t)S.ld;
+  {
+    const int pos = UNIT * lane, inrow = pos % KB;   // byte in the instruction's rows
 #pragma unroll
-  for (int h = 0; h < kDma; ++h) {
-    const int pos = UNIT * lane;   // byte in the instruction's rows
-    const int r = 32 * wave + kRowsPerDma * h + pos / KB;
-    const int inrow = pos % KB;
-    const uint32_t off = 16 * ((inrow / 16) ^ swz(r)) + inrow % 16;
-    voffA[h] = (uint32_t)min(m0 + r, pM - 1) * rowbytes + off;
-    voffB[h] = (uint32_t)min(n0 + r, pN - 1) * rowbytes + off;
+    for (int h = 0; h < kDmaA; ++h) {
+      const int r = kRowsPerDma * (kDmaA * wave + h) + pos / KB;
+      voffA[h] = (uint32_t)min(m0 + r, pM - 1) * rowbytes + 16 * ((inrow / 16) ^ swz(r)) + inrow % 16;
+    }
+#pragma unroll
+    for (int h = 0; h < kDmaB; ++h) {
+      const int r = kRowsPerDma * (kDmaB * wave + h) + pos / KB;
+      voffB[h] = (uint32_t)min(n0 + r, pN - 1) * rowbytes + 16 * ((inrow / 16) ^ swz(r)) + inrow % 16;
+    }
   }
   const __amdgpu_buffer_rsrc_t rsA =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<uint64_t *>(S.A), 0, (int)((uint32_t)pM * rowbytes), kRawRsrcWord3);
@@ -261,23 +271,24 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   auto issue = [&](int ks, uint8_t *d) {
     const uint32_t so = (uint32_t)(ks * KB);
 #pragma unroll
-    for (int h = 0; h < kDma; ++h) {
-      bdma<UNIT>(rsA, voffA[h] + so, d + (kDma * wave + h) * 64 * UNIT);
-      bdma<UNIT>(rsB, voffB[h] + so, d + TM * KB + (kDma * wave + h) * 64 * UNIT);
+    for (int h = 0; h < kDmaB; ++h) {
+      if (h < kDmaA) bdma<UNIT>(rsA, voffA[h < kDmaA ? h : 0] + so, d + (kDmaA * wave + h) * 64 * UNIT);
+      bdma<UNIT>(rsB, voffB[h] + so, d + TM * KB + (kDmaB * wave + h) * 64 * UNIT);
     }
   };
 
-  v16f acc[2][2];
+  v16f acc[FA][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < FA; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = (v16f){};
 
   // operand words of one K step: [c][i] for its two 256-element chunks;
   // lane (r, h) holds elements 256 c + 128 h .. +127 of row r
   struct Ops {
-    uint4 a[2][2], b[2][2];
+    uint4 a[2][FA], b[2][2];
     uint4 bc[2];   // the B fragment this wave counts (fragment wm), per chunk
+    uint4 ac;      // FA = 1: the chunk of the A fragment this wave counts (chunk wn)
   };
   const int arow = lane & 31, ahalf = lane >> 5;
   // Register fragment i of a wave's A operands holds tile fragment i ^ wn
@@ -286,7 +297,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // no select per word.  acc[i][j] holds tile rows of fragment i ^ wn.  (The
   // same order for the B fragments by wm measured slower: the compiler then
   // waits for every LDS read early in each K step.)
-  const int xa = wn;
+  const int xa = FA == 2 ? wn : 0;
   auto read = [&](Ops &o, const uint8_t *t) {
     const uint8_t *tA = t, *tB = t + TM * KB;
 #pragma unroll
@@ -294,12 +305,16 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       const int u = 2 * c + ahalf;   // 16-byte unit of the 64-byte row
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int ra_ = wm * 64 + (i ^ xa) * 32 + arow, rb_ = wn * 64 + i * 32 + arow;
-        o.a[c][i] = *reinterpret_cast<const uint4 *>(&tA[ra_ * KB + ((u ^ swz(ra_)) * 16)]);
+        const int ra_ = wm * 32 * FA + (i ^ xa) * 32 + arow, rb_ = wn * 64 + i * 32 + arow;
+        if (i < FA) o.a[c][i < FA ? i : 0] = *reinterpret_cast<const uint4 *>(&tA[ra_ * KB + ((u ^ swz(ra_)) * 16)]);
         o.b[c][i] = *reinterpret_cast<const uint4 *>(&tB[rb_ * KB + ((u ^ swz(rb_)) * 16)]);
       }
       const int rc_ = wn * 64 + wm * 32 + arow;
       o.bc[c] = *reinterpret_cast<const uint4 *>(&tB[rc_ * KB + ((u ^ swz(rc_)) * 16)]);
+    }
+    if constexpr (FA == 1) {
+      const int ra_ = wm * 32 + arow;
+      o.ac = *reinterpret_cast<const uint4 *>(&tA[ra_ * KB + (((2 * wn + ahalf) ^ swz(ra_)) * 16)]);
     }
   };
   // The expanded operands of one K block (c, q) of a step.  A step's MFMAs
@@ -308,11 +323,11 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // and during the last block those of block 0 of the next step, so that the
   // matrix core never waits for an expansion at the start of a step.
   struct Exp {
-    uint4 a[2], b[2];
+    uint4 a[FA], b[2];
   };
   auto expand = [&](const Ops &o, int c, int cls, Exp &e) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i) e.a[i] = class_operand(o.a[c][i], cls);
+    for (int i = 0; i < FA; ++i) e.a[i] = class_operand(o.a[c][i], cls);
 #pragma unroll
     for (int j = 0; j < 2; ++j) e.b[j] = class_operand(o.b[c][j], cls);
   };
@@ -326,7 +341,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       else
         expand(onext, 0, 0, e0next);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < FA; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j) acc[i][j] = mfma_class(e.a[i], e.b[j], acc[i][j], blk & 3);
       if (blk < 7) e = en;
@@ -350,7 +365,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     return bcnt_acc(w.w & m[3], acc);
   };
   auto popc_ops = [&](const Ops &o, const uint32_t (&m0)[4], const uint32_t (&m1)[4]) {
-    pca = popc4(popc4(pca, o.a[0][0], m0), o.a[1][0], m1);
+    if constexpr (FA == 2)
+      pca = popc4(popc4(pca, o.a[0][0], m0), o.a[1][0], m1);
+    else
+      pca = popc4(pca, o.ac, m0);
     pcb = popc4(popc4(pcb, o.bc[0], m0), o.bc[1], m1);
   };
   const uint32_t kFull[4] = {kLowClasses, kLowClasses, kLowClasses, kLowClasses};
@@ -368,13 +386,13 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       uint32_t mv[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) mv[q] = valid[q] & kLowClasses;
-      pca = popc4(pca, o.a[c][0], mv);
+      if (FA == 2 || c == wn) pca = popc4(pca, o.a[c][0], mv);
       pcb = popc4(pcb, o.bc[c], mv);
 #pragma unroll
       for (int cls = 0; cls < 4; ++cls) {
-        uint4 ea[2], eb[2];
+        uint4 ea[FA], eb[2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) ea[i] = class_operand(o.a[c][i], cls);
+        for (int i = 0; i < FA; ++i) ea[i] = class_operand(o.a[c][i], cls);
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
           const uint4 w = o.b[c][j];
@@ -382,7 +400,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
                              class_bits_masked(w.z, valid[2], cls), class_bits_masked(w.w, valid[3], cls));
         }
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < FA; ++i)
 #pragma unroll
           for (int j = 0; j < 2; ++j) acc[i][j] = mfma_class(ea[i], eb[j], acc[i][j], cls);
       }
@@ -442,10 +460,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     // ten MFMAs (issued before them, the reads would share the wait-count
     // of the operands being consumed).
 #pragma unroll
-    for (int i = 0; i < 32; ++i) {
+    for (int i = 0; i < 16 * FA; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-      if (i < 10) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
-      __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);   // VALU
+      if (i < (FA == 2 ? 10 : 9)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // DS read
+      __builtin_amdgcn_sched_group_barrier(0x002, FA == 2 ? 4 : 6, 0);   // VALU
     }
     __builtin_amdgcn_sched_barrier(0);
     popc_ops(cur, kFull, kFull);
@@ -483,8 +501,8 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     const uint32_t ta = pca + (uint32_t)__shfl_xor((int)pca, 32, 64);
     const uint32_t tb = pcb + (uint32_t)__shfl_xor((int)pcb, 32, 64);
     if (lane < 32) {
-      sPc[wm * 64 + wn * 32 + lane] = ta;
-      sPc[TM + wn * 64 + wm * 32 + lane] = tb;
+      sPc[FA == 2 ? wm * 64 + wn * 32 + lane : wn * 64 + wm * 32 + lane] = ta;
+      sPc[128 + wn * 64 + wm * 32 + lane] = tb;
     }
   }
   sP[pw][pr] = pvalid ? prow : 0ull;
@@ -492,7 +510,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   __builtin_amdgcn_s_barrier();
 
   // lane holds z for column n0 + wn*64 + j*32 + (lane & 31) and rows
-  // m0 + wm*64 + i*32 + 8*(e >> 2) + 4*(lane >> 5) + (e & 3) in acc[i][j][e]
+  // m0 + wm*32*FA + i*32 + 8*(e >> 2) + 4*(lane >> 5) + (e & 3) in acc[i][j][e]
   const int lh = lane >> 5, lc = lane & 31;
   // z = acc + (n_low - 2 P_a[row]) + (-2 P_w[column]): a rank-2 term, added
   // exactly by one fp32 MFMA with K = 2 per accumulator (lane l holds A row
@@ -500,15 +518,17 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // A = (n_low - 2 P_a, 1), B = (1, -2 P_w)
   {
     const float nlow = (float)(S.K - S.K / 4);
-    float fa[2], fb[2];
+    float fa[FA], fb[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-      fa[i] = lh == 0 ? nlow - 2.f * (float)sPc[wm * 64 + (i ^ xa) * 32 + lc] : 1.f;
+    for (int i = 0; i < FA; ++i) {
+      const uint32_t pa = FA == 2 ? sPc[wm * 64 + (i ^ xa) * 32 + lc] : sPc[wm * 32 + lc] + sPc[64 + wm * 32 + lc];
+      fa[i] = lh == 0 ? nlow - 2.f * (float)pa : 1.f;
+    }
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      fb[j] = lh == 0 ? 1.f : -2.f * (float)sPc[TM + wn * 64 + j * 32 + lc];
+      fb[j] = lh == 0 ? 1.f : -2.f * (float)sPc[128 + wn * 64 + j * 32 + lc];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FA; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
   }
@@ -521,7 +541,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
 #pragma unroll
   for (int j = 0; j < 2; ++j) colok[j] = __ballot(n0 + wn * 64 + j * 32 + lc < p.N);
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < FA; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
@@ -533,14 +553,14 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       }
   {
     const int i = lane >> 5, j = (lane >> 4) & 1, e = lane & 15;
-    const int rl0 = wm * 64 + (i ^ xa) * 32 + 8 * (e >> 2) + (e & 3);   // the lanes-0-31 row; +4 for 32-63
+    const int rl0 = wm * 32 * FA + (i ^ xa) * 32 + 8 * (e >> 2) + (e & 3);   // the lanes-0-31 row; +4 for 32-63
     const int cw = ((n0 + wn * 64) >> 5) + j;                      // 32-bit word of the 32 columns
     uint32_t *ab32 = reinterpret_cast<uint32_t *>(p.abits);
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int m = m0 + rl0 + 4 * h;
       // columns past N are 0 in the ballot
-      if (m < p.M && cw < 2 * p.words_out) ab32[(size_t)m * 2 * p.words_out + cw] = h ? bhi : blo;
+      if (lane < 32 * FA && m < p.M && cw < 2 * p.words_out) ab32[(size_t)m * 2 * p.words_out + cw] = h ? bhi : blo;
     }
   }
 
@@ -548,7 +568,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     const int gcol0 = n0 + wn * 64;   // the wave's 64 columns
     if (gcol0 < p.N) {
       const int t = gcol0 >> 6;
-      // Key of each of the lane's 32 rows q = 16*i + e over its 2 columns,
+      // Key of each of the lane's 16 FA rows q = 16*i + e over its 2 columns,
       // formed on the bits of the exact fp32 z: with s = -z where the
       // classifier weight is +1 and s = z where it is -1, perceptron k is
       // wrong iff s >= 1.  s is an integer with |s| <= K_{l-1} <= 32767, so
@@ -557,7 +577,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       // the order (|z|, k); every right one (s = +0 wraps, s = -0 and s < 0
       // have the sign bit) gets a key of at least 2^30.
       const uint32_t sh = 31u - (uint32_t)lc;
-      uint32_t v[32];
+      uint32_t v[16 * FA];
       // z as the selection sees it: clipped only where [zlo, zhi] is
       // narrower than every |z| <= 32767 (the saturating variant)
       auto keys = [&](auto clip_tag, auto part_tag, int lo, int hi) {
@@ -565,10 +585,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
         // kPart: only columns [lo, hi) of the wave's 64 take part
         constexpr bool kPart = decltype(part_tag)::value;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < FA; ++i)
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int rl = wm * 64 + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+            const int rl = wm * 32 * FA + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
             const uint64_t rho = sP[wn][rl];
             uint32_t key[2];
 #pragma unroll
@@ -591,29 +611,34 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       // lane its own and its partner's copy of the rows it keeps.  Bits 3..0:
       // DPP row_mirror, row_half_mirror and two quad permutations, each of
       // which pairs a lane with one that differs in that bit.  Afterwards
-      // lane lc holds the minimum over all 64 columns of row q = lc.
+      // lane lc holds the minimum over all 64 columns of row q = lc, or, with
+      // 16 rows, of row q = lc / 2 (lane bit 0 then chooses no row).
       auto lowest = [&]() {
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-          const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 16], false, false);
+        for (int k = 0; k < 8 * FA; ++k) {
+          const auto sw = __builtin_amdgcn_permlane16_swap(v[k], v[k + 8 * FA], false, false);
           v[k] = min((uint32_t)sw[0], (uint32_t)sw[1]);
         }
-        select_step<8, 0x140>(v, lc);   // row_mirror: lane i <-> 15 - i
-        select_step<4, 0x141>(v, lc);   // row_half_mirror: lane i <-> 7 - i
-        select_step<2, 0x4E>(v, lc);    // quad_perm [2,3,0,1]
-        select_step<1, 0xB1>(v, lc);    // quad_perm [1,0,3,2]
+        select_step<4 * FA, 8, 0x140>(v, lc);   // row_mirror: lane i <-> 15 - i
+        select_step<2 * FA, 4, 0x141>(v, lc);   // row_half_mirror: lane i <-> 7 - i
+        select_step<FA, 2, 0x4E>(v, lc);        // quad_perm [2,3,0,1]
+        if constexpr (FA == 2)
+          select_step<1, 1, 0xB1>(v, lc);       // quad_perm [1,0,3,2]
+        else
+          v[0] = min(v[0], (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v[0], 0xB1, 0xF, 0xF, false));
         return v[0];
       };
-      const int i = lc >> 4, e = lc & 15;
-      const int rl = wm * 64 + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+      const int q = FA == 2 ? lc : lc >> 1, i = q >> 4, e = q & 15;
+      const int rl = wm * 32 * FA + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
       const int m = m0 + rl;
+      const bool writes = m < p.M && (FA == 2 || (lc & 1) == 0);
       if (p.mode == kFwdFusedSelect) {   // the wave's columns are one group
         if (clip)
           keys(std::true_type{}, std::false_type{}, 0, 64);
         else
           keys(std::false_type{}, std::false_type{}, 0, 64);
         const uint32_t key = lowest();
-        if (m < p.M) p.kstar[(size_t)t * p.ldk + m] = key >= (1u << 27) ? (int16_t)-1 : (int16_t)(key & 0x3Fu);
+        if (writes) p.kstar[(size_t)t * p.ldk + m] = key >= (1u << 27) ? (int16_t)-1 : (int16_t)(key & 0x3Fu);
       } else {                           // columns [0, end) of one group, [end, 64) of the next
         const int end = p.gamma - gcol0 % p.gamma, cols = min(64, p.N - gcol0);
         for (int h = 0; h < (end < 64 ? 2 : 1); ++h) {
@@ -623,19 +648,19 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
           else
             keys(std::false_type{}, std::true_type{}, lo, hi);
           const uint32_t key = lowest();
-          if (m < p.M) p.part[(size_t)(2 * t + h) * p.M + m] = key;
+          if (writes) p.part[(size_t)(2 * t + h) * p.M + m] = key;
         }
       }
     }
   } else if (p.mode == kFwdWriteZ || p.mode == kFwdWriteZ32) {
     const bool wide = p.mode == kFwdWriteZ32;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < FA; ++i)
 #pragma unroll
       for (int j = 0; j < 2; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-          const int m = m0 + wm * 64 + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
+          const int m = m0 + wm * 32 * FA + (i ^ xa) * 32 + 8 * (e >> 2) + 4 * lh + (e & 3);
           const int col = n0 + wn * 64 + j * 32 + lc;
           if (m < p.M && col < p.N) {
             const size_t o = (size_t)m * p.ldz + col;
@@ -650,6 +675,17 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
 }
 
 }  // namespace
+
+// Tiles of 64 rows where they still find a compute unit each (at most one
+// wave per SIMD): each then has half the matrix work, and twice as many units
+// share it.  Per launch, 128-row tiles -> 64-row tiles (us, inference over
+// equal widths): 256 x 8192 (128 tiles of 128 rows): 14.1 -> 10.7; 512 x
+// 4096: 9.5 -> 7.6; 1024 x 2048: 7.5 -> 6.2; past 256 tiles of 64 rows 320
+// x 8192: 14.0 against 15.4, 640 x 4096: 9.6 against 9.7, 1024 x 4096: 10.1
+// against 10.5.
+bool half_rows(const FwdArgs &a) {
+  return (long long)a.nslices * ((a.M + 63) / 64) * ((a.N + TN - 1) / TN) <= 256;
+}
 
 hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
@@ -681,7 +717,8 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
     bytes_a += (double)a.M * q.ld;
     bytes_b += (double)a.N * q.ld;
   }
-  a.nt_m = (a.M + TM - 1) / TM;
+  const int fa = half_rows(a) ? 1 : 2;
+  a.nt_m = (a.M + 64 * fa - 1) / (64 * fa);
   a.nt_n = (a.N + TN - 1) / TN;
   // each XCD keeps its slice of the larger operand in its own L2 (W_l in a
   // hidden layer; a_l when B is a narrow classifier matrix P_l)
@@ -706,14 +743,22 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
   const dim3 grid(a.nslices * a.nt_m * a.nt_n);
   const FwdSlice &s0 = a.sl[0];
 #define BMLP_FWD_ARGS s0.A, s0.B, a.y, s0.ld, s0.K, a.M, a.N, a.nt_m, a.nt_n, a.xcd_remap, a.ystride, a.mode, a
-  if (aligned && sliced)
-    hipLaunchKernelGGL((fwd_fp4_kernel<16, true>), grid, dim3(256), 0, s, BMLP_FWD_ARGS);
+#define BMLP_FWD_LAUNCH(FA_, UNIT_)                                                             \
+  do {                                                                                        \
+    if (sliced)                                                                               \
+      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, true>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
+    else                                                                                      \
+      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, false>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
+  } while (0)
+  if (aligned && fa == 2)
+    BMLP_FWD_LAUNCH(2, 16);
   else if (aligned)
-    hipLaunchKernelGGL((fwd_fp4_kernel<16, false>), grid, dim3(256), 0, s, BMLP_FWD_ARGS);
-  else if (sliced)
-    hipLaunchKernelGGL((fwd_fp4_kernel<4, true>), grid, dim3(256), 0, s, BMLP_FWD_ARGS);
+    BMLP_FWD_LAUNCH(1, 16);
+  else if (fa == 2)
+    BMLP_FWD_LAUNCH(2, 4);
   else
-    hipLaunchKernelGGL((fwd_fp4_kernel<4, false>), grid, dim3(256), 0, s, BMLP_FWD_ARGS);
+    BMLP_FWD_LAUNCH(1, 4);
+#undef BMLP_FWD_LAUNCH
 #undef BMLP_FWD_ARGS
   return hipGetLastError();
 }

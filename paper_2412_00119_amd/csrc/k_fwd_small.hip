@@ -300,14 +300,15 @@ void launch_shape(bool sliced, dim3 grid, int nt_m, int nt_n, int per, const Fwd
 // flight at once.  Per launch, inference over equal widths (launches of 128 x
 // 128 tiles -> this kernel, us including the dependent launch): n = 1, K =
 // 4096: 8.0 -> 4.8; 256 x 1024: 5.5 -> 3.7; 512 x 2048: 6.4 -> 4.9 (512
-// tiles); past 512 tiles 1024 x 2048: 6.5 against 6.9, 512 x 4096: 8.7
-// against 9.5.  With few chunks the tiles are cheap enough for twice as many:
-// 2048 x 768: 5.3 -> 3.9, 2048 x 1024: 5.1 -> 4.9.
+// tiles); past 512 tiles (64 x 128 tiles of fwd_fp4_kernel against this kernel)
+// 640 x 2048: 5.4 against 5.5, 512 x 4096: 6.9 against 9.6.  With few
+// chunks the tiles are cheap enough for half as many more: 1536 x 1024
+// (768 tiles): 4.6 against 4.5, 2048 x 1024: 4.6 against 4.9.
 bool fwd_small_wins(const FwdArgs &a) {
   const long long tiles = (long long)a.nslices * ((a.M + TM - 1) / TM) * ((a.N + kCols - 1) / kCols);
   int kmax = 0;
   for (int i = 0; i < a.nslices; ++i) kmax = a.sl[i].K > kmax ? a.sl[i].K : kmax;
-  return tiles <= (kmax <= 256 * kWaves ? 1024 : 512);
+  return tiles <= (kmax <= 256 * kWaves ? 768 : 512);
 }
 
 // Arguments as launch_fwd_fp4 has checked and completed them.

@@ -49,3 +49,21 @@ def test_many_class_products(c, n):
         z = a @ p.ora.W(l).astype(np.int64).T
         a = np.where(z >= 0, 1, -1)
         np.testing.assert_array_equal(out[l - 1].cpu().numpy(), a @ p.ora.P[l - 1].astype(np.int64).T)
+
+
+@pytest.mark.parametrize("k0,k1,gamma,n", [
+    (1024, 4096, 64, 449),    # 256 tiles of 64 rows, one row in the last; K without a remainder
+    (1200, 4096, 64, 500),    # rows of 19 words (four-byte loads)
+    (1200, 4096, 64, 520),    # 288 tiles of 64 rows: tiles of 128
+    (1130, 4030, 65, 449),    # a column tail, groups across tiles
+    (2600, 2304, 0, 900),     # the group-size rule, row tail 4
+    (513, 8128, 127, 225),    # K one past a step, 64 column tiles
+])
+def test_forward_half_tiles(k0, k1, gamma, n):
+    """The 64-row tiles of the large-tile kernel, and the line to its 128-row tiles."""
+    test_forward_shapes(k0, k1, gamma, n)
+
+
+def test_many_class_products_half_tiles():
+    """y_hat of three layers in one launch of 243 tiles of 64 rows."""
+    test_many_class_products(300, 1700)
