@@ -172,7 +172,9 @@ int forward_layers(bmlp_ctx *ctx, const uint64_t *x, int n, hipStream_t s, int32
     return reinterpret_cast<uint64_t *>(a_rows ? a_rows + a_rows_offset(p, n, l) : ctx->ws + p.layer[l - 1].off_a);
   };
   if (use_mfma(p)) {
-    const bool cls_gemm = p.c > kClsMaxClasses;
+    // y_hat by the forward's contraction: many classes, or so few patterns that
+    // rows of P_l spread over the chip are quicker than tiles of 16 patterns
+    const bool cls_gemm = p.c > kClsMaxClasses || (!correct && n <= kFwdRowsMax);
     int16_t *y16_ws = reinterpret_cast<int16_t *>(ctx->ws + p.off_yhat);
     ClsGemm gemm(p, n, correct == nullptr);
     const uint64_t *a_prev = x;

@@ -93,6 +93,11 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s);
 // launch_fwd_fp4 only).
 bool fwd_small_wins(const FwdArgs &a);
 hipError_t launch_fwd_small(const FwdArgs &a, hipStream_t s);
+// The same for at most kFwdRowsMax patterns: sign bits alone (kFwdPlain) or
+// z alone (kFwdWriteZ32).
+constexpr int kFwdRowsMax = 4;
+bool fwd_rows_wins(const FwdArgs &a);
+hipError_t launch_fwd_rows(const FwdArgs &a, hipStream_t s);
 
 // Classifier on the matrix cores, then the local error signal, for up to
 // kMaxClsLayers layers in one launch (ceil(n / 16) work-groups per layer),

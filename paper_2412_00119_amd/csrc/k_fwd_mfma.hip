@@ -739,6 +739,7 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
     a.c = 1;
     a.pw_max = 0;
   }
+  if (fwd_rows_wins(a)) return launch_fwd_rows(a, s);
   if (fwd_small_wins(a)) return launch_fwd_small(a, s);
   const dim3 grid(a.nslices * a.nt_m * a.nt_n);
   const FwdSlice &s0 = a.sl[0];
