@@ -22,7 +22,7 @@ constexpr int kStreamExpand = 5;
 //
 // What bounds it: a work-group touches one cache line per row and F bytes, and
 // a compute unit fills a line in two cycles and adds to 64 LDS counters in
-// about eight.  So:
+// about 16.  So:
 //   * F = 16 where rows can be split, so that a line is touched half as often
 //     and every compute unit has rows to count; F = 8 where they cannot,
 //     since the features alone must fill the chip then;
@@ -280,14 +280,14 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
 //   * x is staged through LDS with the bytes of each 32 inputs transposed to
 //     match (dword s holds inputs s, s + 8, s + 16, s + 24), 16 v_perm_b32
 //     per 32 bytes once for all columns.  Rows are 128 + 16 bytes apart, so
-//     that 16-byte reads at one row per lane hit every bank once; the next
-//     stage's global loads are in flight while one is computed.
+//     that 16-byte reads at one row per lane hit every bank once; the global
+//     loads of the next two stages are in flight while one is computed.
 //   * R's bits for kXChunk inputs of the 128 columns are drawn into LDS as
 //     whole Philox blocks; the columns' bit offsets in them are taken out by
 //     one v_alignbit_b32 per word read.  They are drawn once per work-group
 //     when all inputs fit one chunk.
 // Exact: |acc| <= 128 * 65536.
-// 10000 x 784 -> 3072: 1342 -> 52 us (the kernel before summed 4 inputs at a
+// 10000 x 784 -> 3072: 1342 -> 47 us (the kernel before summed 4 inputs at a
 // time with v_dot4_i32_i8, rebuilding the +-1 bytes for every pattern).
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -344,105 +344,57 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
 
   // a thread stages 64 bytes of one row: words 2 (tid & 1), + 1 of the stage
   const int srow = tid >> 1, sbyte = 64 * (tid & 1);
-  for (int rt = (int)blockIdx.y; rt < row_tiles; rt += (int)gridDim.y) {
-    const int m0 = rt * kXTile;
-    const int8_t *xr = x + (size_t)min(m0 + srow, n - 1) * k_raw;   // rows past n repeat the last one
-    uint4 v[4];
-    int sum = 0;
-    auto load = [&](int st) {
-      const int i = st * kXStage + sbyte;
-      if (i + 64 <= k_raw) {
+  // The stages of the work-group's row tiles run as one sequence, two of them
+  // in registers ahead of the one that is computed: the first stages of a
+  // tile are loaded during the last ones of the tile before.
+  int rt = (int)blockIdx.y, st = 0;     // computed next
+  int lrt = rt, lst = 0;                // loaded next
+  int sum = 0;
+  v16i acc[2][2];
+  // the lane's columns: where their bits start in sR
+  int base[2];
+  uint32_t sh[2];
+  auto load = [&](uint4 (&v)[4]) {
+    // rows past n repeat the last one; what is loaded past the last tile is not used
+    const int8_t *xr = x + (size_t)min(lrt * kXTile + srow, n - 1) * k_raw;
+    const int i = lst * kXStage + sbyte;
+    if (i + 64 <= k_raw) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], xr + i + 16 * q, 16);
-      } else {   // the row's end: zeros past it
+      for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], xr + i + 16 * q, 16);
+    } else {   // the row's end: zeros past it
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          uint32_t w[4] = {0u, 0u, 0u, 0u};
-          const int left = k_raw - (i + 16 * q);
-          if (left >= 16) {
-            __builtin_memcpy(w, xr + i + 16 * q, 16);
-          } else {
+      for (int q = 0; q < 4; ++q) {
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        const int left = k_raw - (i + 16 * q);
+        if (left >= 16) {
+          __builtin_memcpy(w, xr + i + 16 * q, 16);
+        } else {
 #pragma unroll
-            for (int b = 0; b < 16; ++b)
-              if (b < left) w[b >> 2] |= (uint32_t)(uint8_t)xr[i + 16 * q + b] << (8 * (b & 3));
-          }
-          v[q] = make_uint4(w[0], w[1], w[2], w[3]);
+          for (int b = 0; b < 16; ++b)
+            if (b < left) w[b >> 2] |= (uint32_t)(uint8_t)xr[i + 16 * q + b] << (8 * (b & 3));
         }
-      }
-    };
-    auto store = [&](uint8_t *d) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const uint4 a = v[2 * h], b = v[2 * h + 1];
-        const uint32_t d8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) sum = __builtin_amdgcn_sdot4((int)d8[q], 0x01010101, sum, false);
-        uint4 *o = reinterpret_cast<uint4 *>(d + srow * kXLd + sbyte + 32 * h);
-        o[0] = transpose4(d8[0], d8[2], d8[4], d8[6]);
-        o[1] = transpose4(d8[1], d8[3], d8[5], d8[7]);
-      }
-    };
-
-    v16i acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = (v16i){};
-    // the lane's columns: where their bits start in sR
-    int base[2];
-    uint32_t sh[2];
-    load(0);
-    for (int st = 0; st < ns; ++st) {
-      if (st % kChunkStages == 0) {
-        const int i0 = st * kXStage;
-        if (ns > kChunkStages || rt == (int)blockIdx.y) {
-          __syncthreads();   // the chunk before is no longer read
-          draw(i0);
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int c = wn * 64 + j * 32 + lc;
-          const uint32_t off = (uint32_t)((uint64_t)(j0 + c) * (uint64_t)k_raw + (uint64_t)i0) & 127u;
-          base[j] = c * kXWords + (int)(off >> 5);
-          sh[j] = off & 31u;
-        }
-      }
-      store(sX[st & 1]);
-      __syncthreads();
-      if (st + 1 < ns) load(st + 1);
-      const uint8_t *t = sX[st & 1];
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const int w = 2 * ks + lh;   // the lane's 32 inputs of the stage
-        uint4 a[2][2];
-        uint32_t r[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const uint4 *p = reinterpret_cast<const uint4 *>(t + (wm * 64 + i * 32 + lc) * kXLd + 32 * w);
-          a[i][0] = p[0];
-          a[i][1] = p[1];
-        }
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const uint32_t *p = sR + base[j] + 4 * (st % kChunkStages) + w;
-          r[j] = __builtin_amdgcn_alignbit(p[1], p[0], sh[j]);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          v4i eb[2];
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) eb[j][q] = (int)((r[j] >> (4 * h + q)) & 0x01010101u);
-#pragma unroll
-          for (int i = 0; i < 2; ++i) {
-            const v4i ea = {(int)a[i][h].x, (int)a[i][h].y, (int)a[i][h].z, (int)a[i][h].w};
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ea, eb[j], acc[i][j], 0, 0, 0);
-          }
-        }
+        v[q] = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
+    if (++lst == ns) {
+      lst = 0;
+      lrt = min(lrt + (int)gridDim.y, row_tiles - 1);
+    }
+  };
+  auto store = [&](const uint4 (&v)[4], uint8_t *d) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const uint4 a = v[2 * h], b = v[2 * h + 1];
+      const uint32_t d8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sum = __builtin_amdgcn_sdot4((int)d8[q], 0x01010101, sum, false);
+      uint4 *o = reinterpret_cast<uint4 *>(d + srow * kXLd + sbyte + 32 * h);
+      o[0] = transpose4(d8[0], d8[2], d8[4], d8[6]);
+      o[1] = transpose4(d8[1], d8[3], d8[5], d8[7]);
+    }
+  };
+
+  auto epilogue = [&]() {
     sum += __shfl_xor(sum, 1, 64);
     if ((tid & 1) == 0) sSum[srow] = sum;
     __syncthreads();
@@ -473,9 +425,78 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
     const int cw = ((j0 + wn * 64) >> 5) + j;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + (e & 3) + 4 * h;
+      const int m = rt * kXTile + wm * 64 + i * 32 + 8 * (e >> 2) + (e & 3) + 4 * h;
       if (m < n && cw < words32) bits[(size_t)m * words32 + cw] = h ? bhi : blo;
     }
+  };
+  auto stage = [&](uint4 (&v)[4], uint8_t *t) {
+    if (st == 0) {
+      sum = 0;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = (v16i){};
+    }
+    if (st % kChunkStages == 0) {
+      const int i0 = st * kXStage;
+      if (ns > kChunkStages || rt == (int)blockIdx.y) {
+        __syncthreads();   // the chunk before is no longer read
+        draw(i0);
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int c = wn * 64 + j * 32 + lc;
+        const uint32_t off = (uint32_t)((uint64_t)(j0 + c) * (uint64_t)k_raw + (uint64_t)i0) & 127u;
+        base[j] = c * kXWords + (int)(off >> 5);
+        sh[j] = off & 31u;
+      }
+    }
+    store(v, t);
+    __syncthreads();
+    load(v);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int w = 2 * ks + lh;   // the lane's 32 inputs of the stage
+      uint4 a[2][2];
+      uint32_t r[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const uint4 *p = reinterpret_cast<const uint4 *>(t + (wm * 64 + i * 32 + lc) * kXLd + 32 * w);
+        a[i][0] = p[0];
+        a[i][1] = p[1];
+      }
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const uint32_t *p = sR + base[j] + 4 * (st % kChunkStages) + w;
+        r[j] = __builtin_amdgcn_alignbit(p[1], p[0], sh[j]);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        v4i eb[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) eb[j][q] = (int)((r[j] >> (4 * h + q)) & 0x01010101u);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const v4i ea = {(int)a[i][h].x, (int)a[i][h].y, (int)a[i][h].z, (int)a[i][h].w};
+#pragma unroll
+          for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ea, eb[j], acc[i][j], 0, 0, 0);
+        }
+      }
+    }
+    if (++st < ns) return;
+    st = 0;
+    epilogue();
+    rt += (int)gridDim.y;
+  };
+  uint4 v0[4], v1[4];
+  load(v0);
+  load(v1);
+  while (rt < row_tiles) {
+    stage(v0, sX[0]);
+    if (rt >= row_tiles) break;
+    stage(v1, sX[1]);
   }
 }
 
@@ -523,11 +544,12 @@ hipError_t launch_binarize(const int8_t *x, int n, int K, const int8_t *thr, uin
 hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t seed, uint64_t *bits, hipStream_t s) {
   if (n <= 0 || k0 <= 0) return hipSuccess;
   if (k_raw <= 0) return hipErrorInvalidValue;
-  // Enough work-groups for two on each of 256 compute units and a half more
-  // (to even out the last ones); past that a work-group takes more row tiles
-  // and draws its columns' bits once for all of them.
+  // Two work-groups for each of 256 compute units, all running at once; past
+  // that a work-group takes more row tiles and draws its columns' bits once
+  // for all of them.  (10000 x 784 -> 3072: 46.8 us; at most 384 work-groups
+  // 56.0, 640 58.0, 768 53.5, 1024 48.3.)
   const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n + kXTile - 1) / kXTile;
-  const dim3 grid(col_tiles, min(row_tiles, max(1, 768 / col_tiles)));
+  const dim3 grid(col_tiles, min(row_tiles, max(1, 512 / col_tiles)));
   hipLaunchKernelGGL(expand_kernel, grid, dim3(256), 0, s, x, n, k_raw, k0, seed, reinterpret_cast<uint32_t *>(bits),
                      2 * ((k0 + 63) / 64));
   return hipGetLastError();
