@@ -474,9 +474,9 @@ __global__ __launch_bounds__(kThreads, kPerCu * kWaves / 4) void update_kernel(
 
   // work items: (row r, 2048-column chunk); lane l owns 32-column group
   // chunk * 64 + l of the row
-  const int items = (r_hi - r_lo) * U.chunks;
+  const int rows = r_hi - r_lo, items = rows * U.chunks;
   for (int it = wave; it < items; it += kWaves) {
-    const int r = r_lo + it / U.chunks, chunk = it % U.chunks;
+    const int r = r_lo + it % rows, chunk = it / rows;
     const int k = U.perm ? U.perm[g * gamma + r] : g * gamma + r;
     const int cw = chunk * 64 + lane;
     const bool on = cw < U.nw32;
