@@ -158,7 +158,7 @@ struct ClsGemm {
 };
 
 // Forward of every layer for inference (y_hat out) or evaluation (counts:
-// layer l adds to correct[cstride * (l - 1)]; with flags, each pattern's
+// layer l adds to correct[cstride * (l - 1)]; with flags instead each pattern's
 // flag of layer l goes to flags[(l - 1) * max_batch + mu]).  a_rows, if set,
 // replaces the workspace's a_l rows: layer l's n rows start at a_rows +
 // a_rows_offset(p, n, l) (the no-allocation entry point).

@@ -129,7 +129,7 @@ struct ClsLayer {
   uint8_t *err, *upd;               // train
   int32_t *stats;                   // train: this layer's [4], adds [0] and [1]
   int32_t *correct;                 // eval: adds the correct count
-  uint8_t *flag;                    // eval, if set: per pattern, 1 = correct, 2 = tau >= thr
+  uint8_t *flag;                    // eval, if set: per pattern, 1 = correct, 2 = tau >= thr (correct is then left to launch_exit_count)
   SelectMerge merge;                // train: the selection left to merge
 };
 // A batch of a training set: xb[i] = x_all[order[i]], yb[i] = y_all[order[i]]
@@ -174,11 +174,12 @@ struct LossSelectArgs {
 hipError_t launch_loss_select(const LossSelectArgs &a, hipStream_t s);
 
 // correct[0] += #(argmax yhat == y)
-// flag, if set: per pattern, 1 = correct, 2 = the margin tau reaches thr
+// flag, if set: per pattern, 1 = correct, 2 = the margin tau reaches thr, and
+// the correct counts are left to launch_exit_count.
 hipError_t launch_eval_count(const int32_t *yhat, int c, const int32_t *y, int n, int32_t *correct,
                              uint8_t *flag, int thr, hipStream_t s);
-// Early exits from the per-layer flags [L][ldf] (see launch_eval_count):
-// counts[l][1] += patterns whose first layer with flag & 2 (or the last
+// Correct counts and early exits from the per-layer flags [L][ldf] (see
+// launch_eval_count): counts[l][0] += patterns with flag & 1, counts[l][1] += patterns whose first layer with flag & 2 (or the last
 // layer) is l, counts[l][2] += those of them with flag & 1.
 hipError_t launch_exit_count(const uint8_t *flags, int ldf, int L, int n, int32_t *counts, hipStream_t s);
 hipError_t launch_gather_batch(const GatherArgs &a, hipStream_t s);

@@ -348,9 +348,10 @@ __global__ __launch_bounds__(64 * kWaves) void cls_fp4_kernel(int pn, int pc, in
       t = merge(t, dpp_top2<0x140>(t));   // row_mirror
       if (li == 0) {
         if (mode == kClsEval) {
-          if (t.i1 == label) atomicAdd(&cnt[2], 1);
           if (flag_out != nullptr)
             flag_out[mu] = (uint8_t)((t.i1 == label ? 1 : 0) | ((t.v1 - t.v2) >= thr ? 2 : 0));
+          else if (t.i1 == label)
+            atomicAdd(&cnt[2], 1);
         } else {
           const bool err = t.i1 != label;
           const bool upd = err || (t.v1 - t.v2) < thr;
@@ -432,9 +433,10 @@ __global__ __launch_bounds__(64 * kArgWaves) void cls_argmax_kernel(ClsBatch p) 
     if (lane == 0) {
       const int label = p.y[mu];
       if (p.mode == kClsEval) {
-        if (t.i1 == label) atomicAdd(&cnt[2], 1);
         if (Lr.flag != nullptr)
           Lr.flag[mu] = (uint8_t)((t.i1 == label ? 1 : 0) | ((t.v1 - t.v2) >= Lr.thr ? 2 : 0));
+        else if (t.i1 == label)
+          atomicAdd(&cnt[2], 1);
       } else {
         const bool err = t.i1 != label;
         const bool upd = err || (t.v1 - t.v2) < Lr.thr;
