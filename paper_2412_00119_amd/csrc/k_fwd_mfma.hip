@@ -305,8 +305,11 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       const int u = 2 * c + ahalf;   // 16-byte unit of the 64-byte row
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        const int ra_ = wm * 32 * FA + (i ^ xa) * 32 + arow, rb_ = wn * 64 + i * 32 + arow;
-        if (i < FA) o.a[c][i < FA ? i : 0] = *reinterpret_cast<const uint4 *>(&tA[ra_ * KB + ((u ^ swz(ra_)) * 16)]);
+        const int rb_ = wn * 64 + i * 32 + arow;
+        if (i < FA) {
+          const int ra_ = wm * 32 * FA + (FA == 2 ? i ^ xa : 0) * 32 + arow;
+          o.a[c][i < FA ? i : 0] = *reinterpret_cast<const uint4 *>(&tA[ra_ * KB + ((u ^ swz(ra_)) * 16)]);
+        }
         o.b[c][i] = *reinterpret_cast<const uint4 *>(&tB[rb_ * KB + ((u ^ swz(rb_)) * 16)]);
       }
       const int rc_ = wn * 64 + wm * 32 + arow;
