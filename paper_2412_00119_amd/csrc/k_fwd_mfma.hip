@@ -169,7 +169,11 @@ __device__ __forceinline__ void select_step(uint32_t (&v)[N], int lc) {
 // the leading 16 dwords of a kernel's arguments are preloaded into scalar
 // registers when the wave starts (kernarg preloading), so the tile's first
 // loads do not wait for a read of the argument buffer.
-template <int FA, int UNIT, bool SLICED>
+// KIND: what the epilogue writes, so that a kernel holds no code (nor label and
+// rho loads) of the others: kTrain a_l with a selection, or z of one layer;
+// kSliced z of several layers; kPlain a_l alone.
+enum { kTrain = 0, kSliced = 1, kPlain = 2 };
+template <int FA, int UNIT, int KIND>
 __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const uint64_t *pB, const int32_t *py, int pld,
                                                       int pK, int pM, int pN, int pnt_m, int pnt_n, int pxcd,
                                                       int pystride, int pmode, FwdArgs p) {
@@ -178,6 +182,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   // slots the direct-to-LDS loads are still filling (it tells apart at most
   // eight such arrays).  66 KB in all: two work-groups fit on a CU.
   constexpr int TM = 64 * FA;
+  constexpr bool SLICED = KIND == kSliced, kSelects = KIND == kTrain;
   constexpr int kSlot = (TM + TN) * KB;
   __shared__ __align__(16) uint8_t s0[kSlot], s1[kSlot], s2[kSlot], s3[kSlot];
   __shared__ uint64_t sP[2][TM];       // rho^{y^mu} bits of the tile's 128 columns, per group
@@ -427,7 +432,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   const int nks = (S.K + 511) / 512;
   const int nfull = S.K / 512;      // steps with no element past K
   const int klast = nks - 1;        // nks >= 1
-  if (wave == 0) {   // labels first: the oldest loads, covered by the prologue's wait
+  if (kSelects && wave == 0) {   // labels first: the oldest loads, covered by the prologue's wait
 #pragma unroll
     for (int h = 0; h < TM / 64; ++h)
       dma<4>(py + (size_t)min(m0 + 64 * h + lane, pM - 1) * pystride, sY + 64 * h);
@@ -442,8 +447,11 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   read(r0, s0);
   Exp e0, e1;
   expand(r0, 0, 0, e0);
-  const int yl = min(max(sY[pr], 0), p.c - 1);   // stay inside P on a bad label
-  const uint64_t prow = p.P[(size_t)yl * p.ldp + min(pwg, p.pw_max)];
+  uint64_t prow = 0ull;
+  if constexpr (kSelects) {
+    const int yl = min(max(sY[pr], 0), p.c - 1);   // stay inside P on a bad label
+    prow = p.P[(size_t)yl * p.ldp + min(pwg, p.pw_max)];
+  }
   __builtin_amdgcn_sched_barrier(0);
   // The sched_barrier(0) fences pin the order of the phases; otherwise the
   // scheduler sinks the read-ahead to its use and the LDS latency reappears.
@@ -508,7 +516,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
       sPc[128 + wn * 64 + wm * 32 + lane] = tb;
     }
   }
-  sP[pw][pr] = pvalid ? prow : 0ull;
+  if constexpr (kSelects) sP[pw][pr] = pvalid ? prow : 0ull;
   __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0) only
   __builtin_amdgcn_s_barrier();
 
@@ -567,7 +575,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
     }
   }
 
-  if (p.mode == kFwdFusedSelect || p.mode == kFwdSelectParts) {
+  if (kSelects && (p.mode == kFwdFusedSelect || p.mode == kFwdSelectParts)) {
     const int gcol0 = n0 + wn * 64;   // the wave's 64 columns
     if (gcol0 < p.N) {
       const int t = gcol0 >> 6;
@@ -655,7 +663,7 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
         }
       }
     }
-  } else if (p.mode == kFwdWriteZ || p.mode == kFwdWriteZ32) {
+  } else if (KIND != kPlain && (p.mode == kFwdWriteZ || p.mode == kFwdWriteZ32)) {
     const bool wide = p.mode == kFwdWriteZ32;
 #pragma unroll
     for (int i = 0; i < FA; ++i)
@@ -750,9 +758,11 @@ hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
 #define BMLP_FWD_LAUNCH(FA_, UNIT_)                                                             \
   do {                                                                                        \
     if (sliced)                                                                               \
-      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, true>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
+      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, kSliced>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
+    else if (a.mode == kFwdPlain)                                                             \
+      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, kPlain>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
     else                                                                                      \
-      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, false>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
+      hipLaunchKernelGGL((fwd_fp4_kernel<FA_, UNIT_, kTrain>), grid, dim3(256), 0, s, BMLP_FWD_ARGS); \
   } while (0)
   if (aligned && fa == 2)
     BMLP_FWD_LAUNCH(2, 16);
