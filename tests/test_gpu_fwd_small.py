@@ -8,7 +8,7 @@ import pytest
 
 from paper_2412_00119_amd.synth import random_pm1
 
-from gpu_common import Pair, note, torch_cuda
+from gpu_common import Pair, note, pack_np, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -67,3 +67,30 @@ def test_forward_half_tiles(k0, k1, gamma, n):
 def test_many_class_products_half_tiles():
     """y_hat of three layers in one launch of 243 tiles of 64 rows."""
     test_many_class_products(300, 1700)
+
+
+@pytest.mark.parametrize("widths,n", [
+    ((130, 2111, 33), 1900),      # 255 tiles of 128 rows, the last column tile of 63 columns
+    ((600, 4000, 4097), 1025),    # one row and one column past a tile
+    ((64, 8129, 2080), 700),
+])
+def test_inference_column_tails(widths, n):
+    """The large-tile kernel without a selection: signs of ragged widths, and
+    zeros in a_l past the last column."""
+    torch = torch_cuda()
+    rng = np.random.default_rng(sum(widths))
+    note(f"inference {widths} n={n}")
+    p = Pair(widths, 7, 7, n, 1, 0.25, seed=n)
+    x = random_pm1((n, widths[0]), rng)
+    xb, _ = p.to_dev(x)
+    for l in range(1, len(widths)):
+        p.gpu.trace(l, n)["a"].fill_(-1)
+    out = p.gpu.forward(xb)
+    torch.cuda.synchronize()
+    a = x.astype(np.float64)
+    for l in range(1, len(widths)):
+        a = np.where(a @ p.ora.W(l).astype(np.float64).T >= 0, 1.0, -1.0)
+        rows = p.gpu.trace(l, n)["a"].cpu().numpy().view(np.uint64)
+        np.testing.assert_array_equal(rows, pack_np(a.astype(np.int8), rows.shape[1]))
+        want = (a @ p.ora.P[l - 1].astype(np.float64).T).astype(np.int64)
+        np.testing.assert_array_equal(out[l - 1].cpu().numpy(), want)
