@@ -25,3 +25,21 @@ def test_split_rows(widths, gamma, bound, n, variants):
         x = random_pm1((n, widths[0]), rng)
         y = rng.integers(0, 4, n).astype(np.int32)
         p.step(x, y, t, 0.5, tag=f"step {t}")
+
+
+@pytest.mark.parametrize("widths,gamma,n", [
+    ((8300, 64), 64, 90), ((6200, 78), 13, 70), ((33, 4200, 24), 3, 50), ((10300, 12), 1, 40), ((4200, 256), 256, 120),
+])
+def test_rows_of_several_chunks(widths, gamma, n):
+    """Rows of two to six column chunks, which are taken in another order in
+    each chunk, with few rows a work-group and many, when patterns that are
+    alike choose the same few rows."""
+    rng = np.random.default_rng(sum(widths) + n)
+    p = Pair(widths, 3, 31, n, gamma, 0.25, seed=23)
+    protos = random_pm1((3, widths[0]), rng)
+    for t in range(3):
+        note(f"chunks {widths} gamma={gamma} step {t}")
+        y = rng.integers(0, 3, n).astype(np.int32)
+        flip = rng.random((n, widths[0])) < 0.01
+        x = np.where(flip, -protos[y], protos[y]).astype(np.int8)
+        p.step(x, y, t, 0.5, tag=f"step {t}")
