@@ -179,6 +179,51 @@ __global__ __launch_bounds__(256) void median_merge_kernel(const uint4 *__restri
   median_of_bins(c, n, med + f);
 }
 
+// The same where the features alone are several rounds of work-groups for the
+// chip: 64 of them per work-group, a feature per lane.  A work-group of 8
+// features clears and sums as many counters for an eighth of the features,
+// which is most of its time where rows are few.  One histogram per feature,
+// bin-major, so that the 64 lanes of an atomic or a read are in 64 banks; a
+// wave loads 64 bytes of a row at a time, kWideRows rows in flight.  Its 16 waves then
+// take 16 bins each: sums of every feature, and the one whose bins reach the
+// middle looks through them.
+constexpr int kWideFeat = 64, kWideRows = 8, kWideWaves = kMedThreads / 64, kWideBins = 256 / kWideWaves;
+
+__global__ __launch_bounds__(kMedThreads) void feature_median_wide_kernel(const int8_t *__restrict__ x, int n, int K,
+                                                                          int8_t *__restrict__ med) {
+  __shared__ uint32_t hist[256][kWideFeat];
+  __shared__ uint32_t part[kWideWaves][kWideFeat];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int f = (int)blockIdx.x * kWideFeat + lane;
+  for (int i = tid; i < 256 * kWideFeat / 4; i += kMedThreads)
+    reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
+  __syncthreads();
+  const int8_t *col = x + min(f, K - 1);   // lanes past the last feature count it too, into slots of their own
+  uint32_t r = (uint32_t)wave;
+  for (; r + (kWideRows - 1) * kWideWaves < (uint32_t)n; r += kWideRows * kWideWaves) {
+    int v[kWideRows];
+#pragma unroll
+    for (int q = 0; q < kWideRows; ++q) v[q] = col[(size_t)(r + q * kWideWaves) * K];
+#pragma unroll
+    for (int q = 0; q < kWideRows; ++q) atomicAdd(&hist[v[q] + 128][lane], 1u);
+  }
+  for (; r < (uint32_t)n; r += kWideWaves) atomicAdd(&hist[(int)col[(size_t)r * K] + 128][lane], 1u);
+  __syncthreads();
+  uint32_t own = 0u;
+#pragma unroll
+  for (int q = 0; q < kWideBins; ++q) own += hist[kWideBins * wave + q][lane];
+  part[wave][lane] = own;
+  __syncthreads();
+  const uint32_t want = (uint32_t)((n - 1) / 2) + 1u;
+  uint32_t before = 0u;
+  for (int w = 0; w < wave; ++w) before += part[w][lane];
+  if (f < K && before < want && before + own >= want) {
+    int v = kWideBins * wave;
+    while ((before += hist[v][lane]) < want) ++v;   // ends inside the wave's bins
+    med[f] = (int8_t)(v - 128);
+  }
+}
+
 constexpr int kMedFeatSplit = 16, kMedFeat = 8;
 
 inline int med_tiles(int K, int F) { return (K + F - 1) / F; }
@@ -519,6 +564,14 @@ hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, voi
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(median_merge_kernel, dim3((K + 3) / 4), dim3(256), 0, s, static_cast<const uint4 *>(ws), splits, n,
                        K, med);
+    return hipGetLastError();
+  }
+  // Few rows, or features enough to fill the chip 64 at a time.  Work-groups of
+  // 8 features -> of 64, us: 256 rows 784 features 4.7 -> 4.0, 1000 rows 5.2 -> 6.7,
+  // 10000 x 6000: 39.5 -> 44.7, x 8192: 46.5 -> 44.6, x 16384: 87.6 -> 49.5; one
+  // row of 65536: 88.8 -> 6.9.
+  if (n <= 256 || K > 8192) {
+    hipLaunchKernelGGL(feature_median_wide_kernel, dim3(med_tiles(K, kWideFeat)), dim3(kMedThreads), 0, s, x, n, K, med);
     return hipGetLastError();
   }
   const int per_xcd = (med_tiles(K, kMedFeat) + 7) / 8;

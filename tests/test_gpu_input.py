@@ -80,6 +80,14 @@ def test_median_split(n, k):
     np.testing.assert_array_equal(alone.cpu().numpy(), m)
 
 
+@pytest.mark.parametrize("n,k", [(1, 1), (255, 64), (256, 65), (257, 130), (129, 8193), (300, 8191), (128, 8256), (140, 9000),
+                                 (2500, 8200)])
+def test_median_wide(n, k):
+    """64 features per work-group (few rows, or many features): row counts
+    around its passes of 128, feature tails, and columns of extreme values."""
+    test_median_split(n, k)
+
+
 @pytest.mark.parametrize("n,k_raw,k0", [(5, 1, 64), (300, 37, 100), (70, 300, 257), (257, 5000, 64),
                                         (64, 4096, 128)])
 def test_expand(n, k_raw, k0):
