@@ -187,6 +187,10 @@ __global__ __launch_bounds__(256) void median_merge_kernel(const uint4 *__restri
 // wave loads 64 bytes of a row at a time, kWideRows rows in flight.  Its 16 waves then
 // take 16 bins each: sums of every feature, and the one whose bins reach the
 // middle looks through them.
+// A launch counts the threads of a dimension in 32 bits (one past that runs
+// only part of its work-groups, without an error): past kWideGrid work-groups the
+// grid goes on in y.
+constexpr int kWideGrid = 1 << 20;
 constexpr int kWideFeat = 64, kWideRows = 8, kWideWaves = kMedThreads / 64, kWideBins = 256 / kWideWaves;
 
 __global__ __launch_bounds__(kMedThreads) void feature_median_wide_kernel(const int8_t *__restrict__ x, int n, int K,
@@ -194,11 +198,12 @@ __global__ __launch_bounds__(kMedThreads) void feature_median_wide_kernel(const 
   __shared__ uint32_t hist[256][kWideFeat];
   __shared__ uint32_t part[kWideWaves][kWideFeat];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int f = (int)blockIdx.x * kWideFeat + lane;
+  const int f0 = ((int)blockIdx.y * kWideGrid + (int)blockIdx.x) * kWideFeat, left = K - f0;
+  if (left <= 0) return;   // (past the last tile)
   for (int i = tid; i < 256 * kWideFeat / 4; i += kMedThreads)
     reinterpret_cast<uint4 *>(hist)[i] = make_uint4(0u, 0u, 0u, 0u);
   __syncthreads();
-  const int8_t *col = x + min(f, K - 1);   // lanes past the last feature count it too, into slots of their own
+  const int8_t *col = x + f0 + min(lane, left - 1);   // lanes past the last feature count it too, into slots of their own
   uint32_t r = (uint32_t)wave;
   for (; r + (kWideRows - 1) * kWideWaves < (uint32_t)n; r += kWideRows * kWideWaves) {
     int v[kWideRows];
@@ -217,16 +222,16 @@ __global__ __launch_bounds__(kMedThreads) void feature_median_wide_kernel(const 
   const uint32_t want = (uint32_t)((n - 1) / 2) + 1u;
   uint32_t before = 0u;
   for (int w = 0; w < wave; ++w) before += part[w][lane];
-  if (f < K && before < want && before + own >= want) {
+  if (lane < left && before < want && before + own >= want) {
     int v = kWideBins * wave;
     while ((before += hist[v][lane]) < want) ++v;   // ends inside the wave's bins
-    med[f] = (int8_t)(v - 128);
+    med[f0 + lane] = (int8_t)(v - 128);
   }
 }
 
 constexpr int kMedFeatSplit = 16, kMedFeat = 8;
 
-inline int med_tiles(int K, int F) { return (K + F - 1) / F; }
+inline int med_tiles(int K, int F) { return (K - 1) / F + 1; }
 
 // Splits of the rows: about two work-groups for each of 256 compute units,
 // with at least one pass of rows each.  A multiple of 8 where the
@@ -571,7 +576,9 @@ hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, voi
   // 10000 x 6000: 39.5 -> 44.7, x 8192: 46.5 -> 44.6, x 16384: 87.6 -> 49.5; one
   // row of 65536: 88.8 -> 6.9.
   if (n <= 256 || K > 8192) {
-    hipLaunchKernelGGL(feature_median_wide_kernel, dim3(med_tiles(K, kWideFeat)), dim3(kMedThreads), 0, s, x, n, K, med);
+    const int tiles = med_tiles(K, kWideFeat);
+    hipLaunchKernelGGL(feature_median_wide_kernel, dim3(min(tiles, kWideGrid), (tiles - 1) / kWideGrid + 1), dim3(kMedThreads),
+                       0, s, x, n, K, med);
     return hipGetLastError();
   }
   const int per_xcd = (med_tiles(K, kMedFeat) + 7) / 8;

@@ -88,6 +88,19 @@ def test_median_wide(n, k):
     test_median_split(n, k)
 
 
+@pytest.mark.parametrize("n,k", [(3, (1 << 25) + 9), (1, (1 << 28) + 70)])
+def test_median_very_wide(n, k):
+    """More features than work-groups of 8 or of 64 fit one launch."""
+    torch = torch_cuda()
+    g = torch.Generator(device="cuda").manual_seed(k)
+    note(f"median n={n} k={k}")
+    x = torch.randint(-128, 128, (n, k), generator=g, device="cuda", dtype=torch.int8)
+    med = B.feature_median(x)
+    want = x[0] if n == 1 else torch.maximum(torch.minimum(x[0], x[1]),
+                                             torch.minimum(torch.maximum(x[0], x[1]), x[2]))
+    assert bool((med == want).all())
+
+
 @pytest.mark.parametrize("n,k_raw,k0", [(5, 1, 64), (300, 37, 100), (70, 300, 257), (257, 5000, 64),
                                         (64, 4096, 128)])
 def test_expand(n, k_raw, k0):
