@@ -284,27 +284,31 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
   const int col = 16 * unit;
   uint16_t *out = reinterpret_cast<uint16_t *>(bits) + unit;
   const int row0 = ((int)blockIdx.y * 4 + wave) * (kBinRows * rpw) + (lane >> lpr_log);
-  if (col + 16 <= K) {
+  if (K >= 16) {
+    // a lane whose columns end past the row loads the row's last 16 and shifts
+    // the bits before its own out, which leaves zeros past column K (byte
+    // loads there, one after another, took 100 x 1000 3.8 -> MEASURE us)
+    const int start = min(col, K - 16), past = min(col - start, 16);
     BinLane t;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       uint32_t w = 0x01010101u;
-      if constexpr (!PM1) __builtin_memcpy(&w, thr + col + 4 * q, 4);
+      if constexpr (!PM1) __builtin_memcpy(&w, thr + start + 4 * q, 4);
       w ^= 0x80808080u;
       t.te[q] = w & 0x00FF00FFu;
       t.to[q] = (w >> 8) & 0x00FF00FFu;
     }
     uint4 v[kBinRows];
 #pragma unroll
-    for (int i = 0; i < kBinRows; ++i) __builtin_memcpy(&v[i], x + (size_t)min(row0 + i * rpw, n - 1) * K + col, 16);
+    for (int i = 0; i < kBinRows; ++i) __builtin_memcpy(&v[i], x + (size_t)min(row0 + i * rpw, n - 1) * K + start, 16);
 #pragma unroll
     for (int i = 0; i < kBinRows; ++i) {
       const int row = row0 + i * rpw;
       if (row < n)
-        out[(size_t)row * 4 * words] = (uint16_t)(ge4(v[i].x, t, 0) | (ge4(v[i].y, t, 1) << 4) |
-                                                  (ge4(v[i].z, t, 2) << 8) | (ge4(v[i].w, t, 3) << 12));
+        out[(size_t)row * 4 * words] = (uint16_t)((ge4(v[i].x, t, 0) | (ge4(v[i].y, t, 1) << 4) |
+                                                   (ge4(v[i].z, t, 2) << 8) | (ge4(v[i].w, t, 3) << 12)) >> past);
     }
-  } else {   // the row's end: byte loads, and zeros past column K
+  } else {   // rows shorter than a load
     for (int i = 0; i < kBinRows; ++i) {
       const int row = row0 + i * rpw;
       if (row >= n) break;

@@ -88,6 +88,13 @@ def test_median_wide(n, k):
     test_median_split(n, k)
 
 
+@pytest.mark.parametrize("n,k", [(100, 1000), (37, 33), (64, 47), (65, 49), (3, 63), (130, 16), (20, 1039)])
+def test_row_tails(n, k):
+    """Rows that end at every place of a lane's 16 columns, and zeros past
+    them in the last word."""
+    test_median_and_binarize_edges(n, k)
+
+
 @pytest.mark.parametrize("n,k", [(3, (1 << 25) + 9), (1, (1 << 28) + 70)])
 def test_median_very_wide(n, k):
     """More features than work-groups of 8 or of 64 fit one launch."""
