@@ -88,7 +88,8 @@ def test_median_wide(n, k):
     test_median_split(n, k)
 
 
-@pytest.mark.parametrize("n,k", [(100, 1000), (37, 33), (64, 47), (65, 49), (3, 63), (130, 16), (20, 1039)])
+@pytest.mark.parametrize("n,k", [(100, 1000), (37, 33), (64, 47), (65, 49), (3, 63), (130, 16), (20, 1039),
+                                 (1, 1), (300, 2), (1025, 13), (77, 15)])
 def test_row_tails(n, k):
     """Rows that end at every place of a lane's 16 columns, and zeros past
     them in the last word."""
