@@ -352,6 +352,9 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
 //     per 32 bytes once for all columns.  Rows are 128 + 16 bytes apart, so
 //     that 16-byte reads at one row per lane hit every bank once; the global
 //     loads of the next two stages are in flight while one is computed.
+//   * rows that end inside a stage (ROW) load the row's last 16 bytes where
+//     fewer are left, and put them in place as they are stored: byte loads
+//     there, one after another, took 1 x 16 -> 256 7.5 us instead of 4.7.
 //   * R's bits for kXChunk inputs of the 128 columns are drawn into LDS as
 //     whole Philox blocks; the columns' bit offsets in them are taken out by
 //     one v_alignbit_b32 per word read.  They are drawn once per work-group
@@ -360,6 +363,7 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
 // 10000 x 784 -> 3072: 1342 -> 47 us (the kernel before summed 4 inputs at a
 // time with v_dot4_i32_i8, rebuilding the +-1 bytes for every pattern).
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kXTile = 128;                      // patterns and output columns of a tile
@@ -379,10 +383,28 @@ __device__ __forceinline__ uint4 transpose4(uint32_t a, uint32_t b, uint32_t c, 
                     __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u), __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u));
 }
 
+// A row's 16 bytes from a place with `left` bytes before the row's end, out of
+// what was loaded there: those bytes, or, with fewer than 16 left, the last 16
+// of the row.
+__device__ __forceinline__ v4u row_end(const v4u &v, int left, int k_raw) {
+  const int s = 16 - (k_raw & 15);   // bytes to drop then, the same for all lanes (16: none are loaded so)
+  const bool one = (s & 4) != 0, two = (s & 8) != 0;
+  const uint32_t a0 = one ? v.y : v.x, a1 = one ? v.z : v.y, a2 = one ? v.w : v.z, a3 = one ? 0u : v.w;
+  const uint32_t b0 = two ? a2 : a0, b1 = two ? a3 : a1, b2 = two ? 0u : a2, b3 = two ? 0u : a3;
+  const uint32_t r = (uint32_t)(s & 3);
+  const v4u e = {__builtin_amdgcn_alignbyte(b1, b0, r), __builtin_amdgcn_alignbyte(b2, b1, r),
+                 __builtin_amdgcn_alignbyte(b3, b2, r), __builtin_amdgcn_alignbyte(0u, b3, r)};
+  return left >= 16 ? v : left > 0 ? e : (v4u)(0u);
+}
+
 // v_writelane_b32 (see the forward kernel)
 extern "C" __device__ uint32_t bmlp_input_writelane(uint32_t v, uint32_t lane, uint32_t old)
     __asm("llvm.amdgcn.writelane.i32");
 
+// ROW: whole stages only (kWhole), or rows that end inside a stage, shorter
+// than a load (kShort, k_raw < 16) or not (kRagged).
+enum { kWhole = 0, kRagged = 1, kShort = 2 };
+template <int ROW>
 __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict__ x, int n, int k_raw, int k0,
                                                         uint64_t seed, uint32_t *__restrict__ bits, int words32) {
   __shared__ __align__(16) uint8_t sX[2][kXTile * kXLd];
@@ -424,37 +446,40 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
   // the lane's columns: where their bits start in sR
   int base[2];
   uint32_t sh[2];
-  auto load = [&](uint4 (&v)[4]) {
+  auto load = [&](v4u (&v)[4]) {
     // rows past n repeat the last one; what is loaded past the last tile is not used
     const int8_t *xr = x + (size_t)min(lrt * kXTile + srow, n - 1) * k_raw;
     const int i = lst * kXStage + sbyte;
-    if (i + 64 <= k_raw) {
+    if constexpr (ROW != kShort) {   // past the row's end its last 16 bytes (see store)
 #pragma unroll
-      for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], xr + i + 16 * q, 16);
-    } else {   // the row's end: zeros past it
+      for (int q = 0; q < 4; ++q) __builtin_memcpy(&v[q], xr + min(i + 16 * q, k_raw - 16), 16);
+    } else {   // bytes, all loads at once
+      uint32_t w[4] = {0u, 0u, 0u, 0u};
+      if (i == 0) {
+        uint8_t c[16];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        const int left = k_raw - (i + 16 * q);
-        if (left >= 16) {
-          __builtin_memcpy(w, xr + i + 16 * q, 16);
-        } else {
+        for (int b = 0; b < 16; ++b) c[b] = (uint8_t)xr[min(b, k_raw - 1)];
 #pragma unroll
-          for (int b = 0; b < 16; ++b)
-            if (b < left) w[b >> 2] |= (uint32_t)(uint8_t)xr[i + 16 * q + b] << (8 * (b & 3));
-        }
-        v[q] = make_uint4(w[0], w[1], w[2], w[3]);
+        for (int b = 0; b < 16; ++b) w[b >> 2] |= (b < k_raw ? (uint32_t)c[b] : 0u) << (8 * (b & 3));
       }
+      v[0] = (v4u){w[0], w[1], w[2], w[3]};
+#pragma unroll
+      for (int q = 1; q < 4; ++q) v[q] = (v4u)(0u);
     }
     if (++lst == ns) {
       lst = 0;
       lrt = min(lrt + (int)gridDim.y, row_tiles - 1);
     }
   };
-  auto store = [&](const uint4 (&v)[4], uint8_t *d) {
+  auto store = [&](const v4u (&v)[4], uint8_t *d) {
+    const bool ends = ROW == kRagged && st == ns - 1;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      const uint4 a = v[2 * h], b = v[2 * h + 1];
+      v4u a = v[2 * h], b = v[2 * h + 1];
+      if (ends) {   // the row's last stage: what a load took from before its place shifted out, zeros past the row
+        a = row_end(a, k_raw - (st * kXStage + sbyte + 32 * h), k_raw);
+        b = row_end(b, k_raw - (st * kXStage + sbyte + 32 * h + 16), k_raw);
+      }
       const uint32_t d8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
       for (int q = 0; q < 8; ++q) sum = __builtin_amdgcn_sdot4((int)d8[q], 0x01010101, sum, false);
@@ -499,7 +524,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
       if (m < n && cw < words32) bits[(size_t)m * words32 + cw] = h ? bhi : blo;
     }
   };
-  auto stage = [&](uint4 (&v)[4], uint8_t *t) {
+  auto stage = [&](v4u (&v)[4], uint8_t *t) {
     if (st == 0) {
       sum = 0;
 #pragma unroll
@@ -560,14 +585,18 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
     epilogue();
     rt += (int)gridDim.y;
   };
-  uint4 v0[4], v1[4];
+  v4u v0[4], v1[4];
   load(v0);
   load(v1);
-  while (rt < row_tiles) {
+  // counted, and the odd stage after the loop: left from its middle, the
+  // compiler copies the stages' registers at its end, after a wait for their
+  // loads (10000 x 1024 -> 3072: 44.8 us so, 40.5 now)
+  int left = ns * ((row_tiles - rt + (int)gridDim.y - 1) / (int)gridDim.y);
+  for (; left >= 2; left -= 2) {
     stage(v0, sX[0]);
-    if (rt >= row_tiles) break;
     stage(v1, sX[1]);
   }
+  if (left) stage(v0, sX[0]);
 }
 
 }  // namespace
@@ -630,8 +659,14 @@ hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t see
   // 56.0, 640 58.0, 768 53.5, 1024 48.3.)
   const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n + kXTile - 1) / kXTile;
   const dim3 grid(col_tiles, min(row_tiles, max(1, 512 / col_tiles)));
-  hipLaunchKernelGGL(expand_kernel, grid, dim3(256), 0, s, x, n, k_raw, k0, seed, reinterpret_cast<uint32_t *>(bits),
-                     2 * ((k0 + 63) / 64));
+  uint32_t *const out = reinterpret_cast<uint32_t *>(bits);
+  const int words32 = 2 * ((k0 + 63) / 64);
+  if (k_raw < 16)
+    hipLaunchKernelGGL((expand_kernel<kShort>), grid, dim3(256), 0, s, x, n, k_raw, k0, seed, out, words32);
+  else if (k_raw % kXStage != 0)
+    hipLaunchKernelGGL((expand_kernel<kRagged>), grid, dim3(256), 0, s, x, n, k_raw, k0, seed, out, words32);
+  else
+    hipLaunchKernelGGL((expand_kernel<kWhole>), grid, dim3(256), 0, s, x, n, k_raw, k0, seed, out, words32);
   return hipGetLastError();
 }
 

@@ -142,6 +142,14 @@ def test_expand_edges(n, k_raw, k0):
     np.testing.assert_array_equal(bits.cpu().numpy().view(np.uint64), pack_np(want, bits.shape[1]))
 
 
+@pytest.mark.parametrize("n", [3, 130])
+@pytest.mark.parametrize("k_raw", [2, 15, 17, 30, 47, 79, 113, 140, 191, 1029])
+def test_expand_row_tails(n, k_raw):
+    """Rows that end at every place of a 16-byte load, and rows shorter than
+    one."""
+    test_expand_edges(n, k_raw, 70)
+
+
 def test_training_on_expanded_inputs():
     torch = torch_cuda()
     p = Pair((256, 128), 5, 15, 64, 64, 0.25, seed=3)
