@@ -232,7 +232,8 @@ def feature_median(x_int8):
     n, K = x_int8.shape
     out = torch.empty(K, dtype=torch.int8, device=x_int8.device)
     wb = bmlp_feature_median_workspace_bytes(n, K)
-    ws = torch.empty(wb, dtype=torch.uint8, device=x_int8.device)
+    # on the launch's own device, whose current stream it is used and given back on
+    ws = torch.empty(wb, dtype=torch.uint8, device="cuda")
     bmlp_feature_median_split(x_int8.data_ptr(), n, K, out.data_ptr(), ws.data_ptr(), wb,
                               torch.cuda.current_stream().cuda_stream)
     return out

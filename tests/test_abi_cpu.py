@@ -179,3 +179,20 @@ def test_epoch_summary_from_counts():
         B.bmlp_epoch_summary(0, 2, L, batch, 0.5)
     with pytest.raises(B.BmlpError):
         B.bmlp_epoch_summary(st.ctypes.data, steps, 0, batch, 0.5)
+
+
+def test_median_scratch_belongs_to_the_launch_stream(monkeypatch):
+    """The scratch memory is given back to the allocator when the call returns,
+    so it must come from the device whose current stream the launches use,
+    which need not be the one that holds the features."""
+    import torch
+
+    empty, made, calls = torch.empty, [], []
+    monkeypatch.setattr(torch, "empty", lambda *a, dtype, device: made.append((dtype, torch.device(device)))
+                        or empty(*a, dtype=dtype))
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: type("Stream", (), {"cuda_stream": 77}))
+    monkeypatch.setattr(B, "bmlp_feature_median_workspace_bytes", lambda n, k: 64)
+    monkeypatch.setattr(B, "bmlp_feature_median_split", lambda *a: calls.append(a))
+    B.feature_median(torch.zeros((4, 3), dtype=torch.int8))
+    assert calls[0][-1] == 77
+    assert made == [(torch.int8, torch.device("cpu")), (torch.uint8, torch.device("cuda"))]
