@@ -313,6 +313,14 @@ def words64(k: int) -> int:
     return (k + 63) // 64
 
 
+def _raw_stream_getter(torch):
+    """Device index -> raw handle of its current stream: without a Stream
+    object around it where torch has that (private) function, else through the
+    public one."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+
+
 class BMLP:
     """A network whose state and workspace live in torch-owned GPU buffers.
 
@@ -346,10 +354,9 @@ class BMLP:
                 raise ValueError("state buffer does not match the configuration")
             self.state = state.to(self.device).contiguous().clone()
         self.ws = torch.empty(wb, dtype=torch.uint8, device=self.device)
-        # the per-call path: the raw handle of the current stream without a
-        # Stream object around it, the C functions, and the shapes that every
-        # call compares with
-        self._raw_stream = torch._C._cuda_getCurrentRawStream
+        # the per-call path: the raw handle of the current stream, the C
+        # functions, and the shapes that every call compares with
+        self._raw_stream = _raw_stream_getter(torch)
         self._lib = lib()
         self._x_words = words64(self.widths[0])
         self._stats_shape = torch.Size((self.n_layers, STATS_STRIDE))

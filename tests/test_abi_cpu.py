@@ -196,3 +196,13 @@ def test_median_scratch_belongs_to_the_launch_stream(monkeypatch):
     B.feature_median(torch.zeros((4, 3), dtype=torch.int8))
     assert calls[0][-1] == 77
     assert made == [(torch.int8, torch.device("cpu")), (torch.uint8, torch.device("cuda"))]
+
+
+def test_stream_handle_without_the_private_function():
+    """A torch without the private function still gives the current stream's
+    handle."""
+    from types import SimpleNamespace as NS
+
+    public = NS(current_stream=lambda index: NS(cuda_stream=1000 + index))
+    assert B._raw_stream_getter(NS(_C=NS(), cuda=public))(3) == 1003
+    assert B._raw_stream_getter(NS(_C=NS(_cuda_getCurrentRawStream=lambda index: index), cuda=public))(3) == 3
