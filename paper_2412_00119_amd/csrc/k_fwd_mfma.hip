@@ -114,9 +114,6 @@ __device__ __forceinline__ void wait_vm() {
 // puts the pass on 64 distinct banks.
 __device__ __forceinline__ int swz(int r) { return (r >> 2) & 3; }
 
-// lane l: A row / B column (l & 31), half (l >> 5) of the 64-element K
-// block; result element i of lane l is row 8*(i>>2) + 4*(l>>5) + (i&3),
-// column (l & 31)
 // K classes (class_bits): the MFMA of class s over a 256-element chunk takes,
 // from each of the lane's four words, the bits of class s in place (nibble t
 // of dword d = bit 4t + s of word d); A and B use the same map, so every
@@ -695,8 +692,6 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
   wait_vm<0>();   // the repeated loads write LDS: they land before the wave ends
 }
 
-}  // namespace
-
 // Tiles of 64 rows where they still find a compute unit each (at most one
 // wave per SIMD): each then has half the matrix work, and twice as many units
 // share it.  Per launch, 128-row tiles -> 64-row tiles (us, inference over
@@ -707,6 +702,8 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
 bool half_rows(const FwdArgs &a) {
   return (long long)a.nslices * ((a.M + 63) / 64) * ((a.N + TN - 1) / TN) <= 256;
 }
+
+}  // namespace
 
 hipError_t launch_fwd_fp4(FwdArgs &a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
