@@ -103,6 +103,27 @@ static void check_layout(const bmlp_config &cfg, const Plan &p) {
   }
 }
 
+// Selection keys that a plan lets into the z scratch stay inside it (y_hat's
+// rows follow).
+static void check_select_parts(const Plan &p) {
+  for (int n : {1, p.max_batch / 2, p.max_batch}) {
+    if (n < 1) continue;
+    size_t bytes = 0;
+    bool parts = true;
+    for (int l = 1; l <= p.L; ++l) {
+      const LayerPlan &lp = p.layer[l - 1];
+      parts = parts && lp.gamma >= 64;
+      // the forward writes keys [2 * 64-column tile + 1][n] at most
+      if (lp.gamma > 64) bytes += (size_t)((lp.k_out + 63) / 64) * 2 * n * 4;
+    }
+    const bool fits = parts && bytes <= p.off_yhat - p.off_z;
+    const bool fit = select_parts_fit(p, n);
+    CHECK(!fit || fits, "%zu bytes of keys in %zu", bytes, p.off_yhat - p.off_z);
+    // (the scratch is rounded up to 256 bytes: keys may be refused within that)
+    CHECK(fit || !parts || bytes + 256 > p.off_yhat - p.off_z, "%zu bytes of keys refused", bytes);
+  }
+}
+
 int main() {
   std::mt19937_64 rng(20241130);
   auto pick = [&](int lo, int hi) { return (int)std::uniform_int_distribution<int>(lo, hi)(rng); };
@@ -139,6 +160,7 @@ int main() {
     if (st == BMLP_OK) {
       ++valid;
       check_layout(cfg, p);
+      check_select_parts(p);
     } else {
       ++invalid;
       CHECK(st == BMLP_EINVAL || st == BMLP_ESHAPE, "status %d", st);
@@ -168,6 +190,34 @@ int main() {
     w[2] = 192;
     CHECK(make_plan(&c, &p) == BMLP_ESHAPE, "shared classifier with unequal widths");
     CHECK(bmlp_describe(nullptr, 1, nullptr) == BMLP_EINVAL, "describe null");
+  }
+
+  // keys of equal layers (75 perceptrons: 16 bytes a pattern and layer; the z
+  // scratch holds 256 bytes a pattern), on either side of the line, and the
+  // networks whose z is stored in the selection's GPU test
+  {
+    auto fit = [&](std::vector<int32_t> w, int max_batch, int n, int gamma) {
+      bmlp_config c{(int)w.size() - 1, w.data(), 4, max_batch, 15, gamma, 0.25, 1, 0, 0};
+      Plan p;
+      CHECK(make_plan(&c, &p) == BMLP_OK, "config of %zu widths", w.size());
+      check_select_parts(p);
+      return select_parts_fit(p, n);
+    };
+    auto equal = [](int k0, int k, int layers) {
+      std::vector<int32_t> w((size_t)layers + 1, k);
+      w[0] = k0;
+      return w;
+    };
+    CHECK(fit(equal(80, 75, 16), 20, 20, 0) && !fit(equal(80, 75, 17), 20, 20, 0), "16 and 17 layers");
+    CHECK(fit(equal(80, 75, 17), 17, 16, 0) && !fit(equal(80, 75, 17), 17, 17, 0), "17 layers, 16 of 17 patterns");
+    CHECK(fit(equal(80, 75, 18), 23, 20, 0) && !fit(equal(80, 75, 18), 23, 23, 0), "18 layers");
+    CHECK(!fit(equal(80, 75, 24), 23, 20, 0) && !fit(equal(80, 75, 24), 23, 18, 0), "24 layers");
+    std::vector<int32_t> mixed{700};
+    for (int i = 0; i < 9; ++i) mixed.insert(mixed.end(), {525, 96});
+    mixed.insert(mixed.end(), 8, 525);
+    CHECK(!fit(mixed, 43, 40, 0) && !fit(mixed, 43, 38, 0), "26 layers of two widths");
+    CHECK(!fit({80, 128, 70}, 20, 1, 2), "groups below 64");
+    CHECK(fit(equal(80, 128, 64), 20, 20, 64), "groups of 64 need no keys");
   }
 
   // the group-size rule's worked examples (Section 4.3), and divisibility

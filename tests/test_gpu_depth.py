@@ -19,7 +19,8 @@ IMPLS = {"popcount": 1, "mfma_fp4": 2}
 DEEP = [
     # widths, c, B, gamma (0: gamma*), n, steps, p_r
     ((70,) + (64,) * 9, 10, 63, 0, 100, 4, 0.5),
-    # gamma*(192) = 96 (the generic selection) among layers of gamma 64;
+    # gamma*(192) = 96 (keys merged by the classifier launch, or z read back on
+    # the popcount route) among layers of gamma 64;
     # eleven layers: launches of eight and three
     ((100, 128, 64, 192, 64, 128, 64, 64, 128, 64, 64, 128), 7, 15, 0, 65, 3, 0.9),
     # sixteen layers: two full launches of eight

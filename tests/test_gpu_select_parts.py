@@ -25,7 +25,9 @@ pytestmark = pytest.mark.gpu
     ((1100, 2100), 105, 9, 600, 0),                     # the large-tile forward
     ((1100, 2100), 105, 9, 600, B.BMLP_VARIANT_SATURATE_Z),
     ((90,) + (96, 64, 81) * 3 + (75,), 0, 4, 20, 0),    # ten layers, some of 64
-    ((80,) + (75,) * 18, 0, 4, 20, 0),                  # keys of 18 layers: stored z
+    ((80,) + (75,) * 18, 0, 4, 20, 0),                  # keys of 18 layers: of 23 patterns they would not fit, of 20 they do
+    ((80,) + (75,) * 24, 0, 4, 20, 0),                  # keys of 24 layers do not: stored z
+    ((700,) + (525, 96) * 9 + (525,) * 8, 0, 4, 40, B.BMLP_VARIANT_SATURATE_Z),   # stored z, clipped
 ])
 def test_select_parts(widths, gamma, c, n, variants):
     rng = np.random.default_rng(sum(widths) + n)

@@ -52,8 +52,19 @@ def test_variant_matches_oracle(name, impl):
 
 @pytest.mark.parametrize("impl", list(IMPLS))
 def test_saturated_selection_with_gamma_star(impl):
-    # gamma* = 105 for 525: the generic selection kernel reads z back
+    # gamma* = 105 for 525: on the matrix cores the forward writes the best
+    # clipped key of each 64-column tile; the popcount route's selection kernel
+    # reads z back
     _run((784, 525), 0, B.BMLP_VARIANT_SATURATE_Z, impl, steps=4)
+
+
+@pytest.mark.parametrize("impl", list(IMPLS))
+@pytest.mark.parametrize("widths,gamma", [((784, 525), 35), ((784, 256, 96), 16), ((784, 510), 1), ((784, 252), 63)])
+def test_saturated_selection_from_stored_z(widths, gamma, impl):
+    # groups below 64: both routes store z, and the selection kernel clips it,
+    # with one, two or four lanes a group
+    p, zmax = _run(widths, gamma, B.BMLP_VARIANT_SATURATE_Z, impl, steps=4)
+    assert zmax > 128      # the clip to [-128, 127] was in play
 
 
 @pytest.mark.parametrize("impl", list(IMPLS))
