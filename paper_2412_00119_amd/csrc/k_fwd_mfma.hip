@@ -695,10 +695,10 @@ __global__ __launch_bounds__(256) void fwd_fp4_kernel(const uint64_t *pA, const 
 // Tiles of 64 rows where they still find a compute unit each (at most one
 // wave per SIMD): each then has half the matrix work, and twice as many units
 // share it.  Per launch, 128-row tiles -> 64-row tiles (us, inference over
-// equal widths): 256 x 8192 (128 tiles of 128 rows): 14.1 -> 10.7; 512 x
-// 4096: 9.5 -> 7.6; 1024 x 2048: 7.5 -> 6.2; past 256 tiles of 64 rows 320
-// x 8192: 14.0 against 15.4, 640 x 4096: 9.6 against 9.7, 1024 x 4096: 10.1
-// against 10.5.
+// equal widths): 256 x 8192 (128 tiles of 128 rows): 13.7 -> 10.4; 512 x
+// 4096: 9.0 -> 7.0; 1024 x 2048: 6.8 -> 5.5; past 256 tiles of 64 rows 320
+// x 8192: 14.2 against 14.9, 640 x 4096: 9.1 against 9.3, 1024 x 4096: 9.7
+// against 9.9.
 bool half_rows(const FwdArgs &a) {
   return (long long)a.nslices * ((a.M + 63) / 64) * ((a.N + TN - 1) / TN) <= 256;
 }

@@ -297,13 +297,14 @@ void launch_shape(bool sliced, dim3 grid, int nt_m, int nt_n, int per, const Fwd
 }  // namespace
 
 // Two work-groups per compute unit, up to which every first load is in
-// flight at once.  Per launch, inference over equal widths (launches of 128 x
-// 128 tiles -> this kernel, us including the dependent launch): n = 1, K =
-// 4096: 8.0 -> 4.8; 256 x 1024: 5.5 -> 3.7; 512 x 2048: 6.4 -> 4.9 (512
-// tiles); past 512 tiles (64 x 128 tiles of fwd_fp4_kernel against this kernel)
-// 640 x 2048: 5.4 against 5.5, 512 x 4096: 6.9 against 9.6.  With few
-// chunks the tiles are cheap enough for half as many more: 1536 x 1024
-// (768 tiles): 4.6 against 4.5, 2048 x 1024: 4.6 against 4.9.
+// flight at once.  Per launch, inference over equal widths (us including the
+// dependent launch; 128 x 128 tiles, 64 x 128 tiles of fwd_fp4_kernel -> this kernel): 8 x
+// 4096: 8.6, 6.5 -> 5.1; 256 x 1024: 5.6, 4.6 -> 3.8; 512 x 2048 (512 tiles): 6.6,
+// 5.3 -> 5.3; past 512 tiles 640 x 2048: 6.7, 5.4 -> 6.0, 512 x 4096: 9.0, 7.1
+// -> 10.4.  With few chunks, half as many tiles more are about even (training
+// step of six layers, 64 x 128 tiles -> this kernel: 1536 x 1024 (768 tiles)
+// 48.9 -> 49.2, 3072 x 512 78.9 -> 74.1, 6144 x 256 102.9 -> 101.4; inference 26.8 ->
+// 29.2, 24.1 -> 26.9, 26.3 -> 25.2).
 bool fwd_small_wins(const FwdArgs &a) {
   const long long tiles = (long long)a.nslices * ((a.M + TM - 1) / TM) * ((a.N + kCols - 1) / kCols);
   int kmax = 0;

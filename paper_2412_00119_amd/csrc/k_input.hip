@@ -256,7 +256,7 @@ int med_splits(int n, int K) {
 // of (x | 0x100) - t is set iff x >= t, and no half borrows from the other.
 // A wave covers 64 / lpr rows by lpr lanes each (lpr a power of two, at most
 // 64), so that narrow rows do not leave lanes idle.
-// 60000 x 784 (47 MB): 107 -> 12.3 us; the kernel before took one byte per
+// 60000 x 784 (47 MB): 103 -> 10.6 us; the kernel before took one byte per
 // lane and one 64-bit word per wave.
 constexpr int kBinRows = 4;
 
@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void binarize_kernel(const int8_t *__restrict_
 //     one v_alignbit_b32 per word read.  They are drawn once per work-group
 //     when all inputs fit one chunk.
 // Exact: |acc| <= 128 * 65536.
-// 10000 x 784 -> 3072: 1342 -> 47 us (the kernel before summed 4 inputs at a
+// 10000 x 784 -> 3072: 1342 -> 39 us (the kernel before summed 4 inputs at a
 // time with v_dot4_i32_i8, rebuilding the +-1 bytes for every pattern).
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
@@ -655,8 +655,8 @@ hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t see
   if (k_raw <= 0) return hipErrorInvalidValue;
   // Two work-groups for each of 256 compute units, all running at once; past
   // that a work-group takes more row tiles and draws its columns' bits once
-  // for all of them.  (10000 x 784 -> 3072: 46.8 us; at most 384 work-groups
-  // 56.0, 640 58.0, 768 53.5, 1024 48.3.)
+  // for all of them.  (10000 x 784 -> 3072: 39.9 us; at most 256 work-groups
+  // 54.9, 384 48.1, 640 48.2, 768 43.5, 1024 40.5.)
   const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n + kXTile - 1) / kXTile;
   const dim3 grid(col_tiles, min(row_tiles, max(1, 512 / col_tiles)));
   uint32_t *const out = reinterpret_cast<uint32_t *>(bits);

@@ -69,7 +69,9 @@ __device__ __forceinline__ Top2 wave_top2(const int32_t *row, int c, int lane) {
 // items of a work-group are neighbouring groups of one pattern, so that the
 // lines of z are used whole.  With one lane per item and gamma dependent
 // steps it took 29 us (100 patterns, 5 groups of 105) and 20 us (500
-// patterns, 25 groups of 81); now 5.0 and 5.3 us.
+// patterns, 25 groups of 81); now 5.0 and 5.3 us.  (On the matrix cores such
+// groups, contiguous and above 64, now come here only where their keys do not
+// fit the z scratch; groups below 64 and reshuffled ones always do.)
 constexpr int kSelThreads = 256;
 
 template <bool PERM>

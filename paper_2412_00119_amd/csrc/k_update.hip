@@ -45,7 +45,8 @@ namespace {
 
 // Work-groups of 12 waves: two of them fit a compute unit together (six
 // waves per SIMD), which hides more of the H loads behind the draws than one
-// work-group of 16 waves per compute unit did.  Each takes half of a group's
+// work-group of 16 waves per compute unit did (measured when a wave held 80
+// registers; now 48, which would let eight waves run).  Each takes half of a group's
 // rows, or less where that leaves compute units idle (split_of).
 constexpr int kWaves = 12;
 constexpr int kThreads = 64 * kWaves;
