@@ -36,6 +36,7 @@ INT8_PEAK_TOPS = 5000.0
 HBM_PEAK_GBS = 8000.0
 ROOT = os.path.dirname(os.path.abspath(__file__))
 FWD_SOURCES = {"fwd_fp4": "paper_2412_00119_amd/csrc/k_fwd_mfma.hip",
+               "fwd_small": "paper_2412_00119_amd/csrc/k_fwd_small.hip",
                "fwd_popcount": "paper_2412_00119_amd/csrc/k_fwd_popcount.hip"}
 
 
@@ -65,6 +66,16 @@ def update_bytes(w):
 def build_sha256(rel):
     from paper_2412_00119_amd.build import kernel_fingerprint
     return kernel_fingerprint(os.path.join(ROOT, rel))
+
+
+def fwd_kernel(w):
+    """The matrix-core forward that the workload's layers run, by the library's
+    line between its two kernels (fwd_small_wins in k_fwd_small.hip): 32 x 64
+    tiles up to 512, or 768 for at most 1024 inputs."""
+    def small(k_in, k_out):
+        return -(-w.batch // 32) * -(-k_out // 64) <= (768 if k_in <= 1024 else 512)
+    kinds = {"fwd_small" if small(a, b) else "fwd_fp4" for a, b in zip(w.widths, w.widths[1:])}
+    return "+".join(sorted(kinds))
 
 
 def measured_traffic(kernel, workload):
@@ -248,7 +259,7 @@ def measure(w, torch, B, steps, warmup, fwd_impl=0, max_batches=48):
         "ms_per_step": ms_step, "ms_per_step_with_kernel_events": ms_prof / steps,
         "samples_per_s": steps * w.batch / (ms / 1e3),
         "mac_per_s": (fwd_macs + cls_macs) * steps / (ms / 1e3), "mac_per_step": fwd_macs + cls_macs,
-        "fwd_roofline": {"kernel": "fwd_fp4" if mfma else "fwd_popcount", "bound": "mfma" if mfma else "alu",
+        "fwd_roofline": {"kernel": fwd_kernel(w) if mfma else "fwd_popcount", "bound": "mfma" if mfma else "alu",
                          "achieved": achieved, "peak": peak, "unit": "TFLOP/s" if mfma else "TOP/s",
                          "frac": achieved / peak, "avg_launch_ms": fwd_avg_ms,
                          "launches": kernels["fwd"]["launches"],
