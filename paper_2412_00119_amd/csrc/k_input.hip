@@ -414,7 +414,7 @@ __global__ __launch_bounds__(256, 2) void expand_kernel(const int8_t *__restrict
   const int wm = wave >> 1, wn = wave & 1, lc = lane & 31, lh = lane >> 5;
   const int j0 = (int)blockIdx.x * kXTile;
   const uint32_t key0 = (uint32_t)seed, key1 = (uint32_t)(seed >> 32);
-  const int ns = (k_raw + kXStage - 1) / kXStage, row_tiles = (n + kXTile - 1) / kXTile;
+  const int ns = (k_raw + kXStage - 1) / kXStage, row_tiles = (n - 1) / kXTile + 1;
   constexpr int kChunkStages = kXChunk / kXStage;
 
   // R's bits of the inputs i0 .. i0 + kXChunk of every column: the Philox
@@ -611,7 +611,7 @@ hipError_t launch_feature_median(const int8_t *x, int n, int K, int8_t *med, voi
   const int splits = ws != nullptr ? med_splits(n, K) : 1;
   if (splits > 1) {
     const int tiles = med_tiles(K, kMedFeatSplit), per_xcd = splits % 8 == 0 ? 0 : (tiles + 7) / 8;   // tiles of each XCD
-    const int rows = (n + splits - 1) / splits;
+    const int rows = (n - 1) / splits + 1;
     hipLaunchKernelGGL((feature_median_kernel<kMedFeatSplit>), dim3((per_xcd ? 8 * per_xcd : tiles) * splits), dim3(kMedThreads), 0, s, x, n,
                        K, med, per_xcd, rows, static_cast<uint4 *>(ws));
     const hipError_t e = hipGetLastError();
@@ -657,7 +657,7 @@ hipError_t launch_expand(const int8_t *x, int n, int k_raw, int k0, uint64_t see
   // that a work-group takes more row tiles and draws its columns' bits once
   // for all of them.  (10000 x 784 -> 3072: 39.9 us; at most 256 work-groups
   // 54.9, 384 48.1, 640 48.2, 768 43.5, 1024 40.5.)
-  const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n + kXTile - 1) / kXTile;
+  const int col_tiles = (k0 + kXTile - 1) / kXTile, row_tiles = (n - 1) / kXTile + 1;
   const dim3 grid(col_tiles, min(row_tiles, max(1, 512 / col_tiles)));
   uint32_t *const out = reinterpret_cast<uint32_t *>(bits);
   const int words32 = 2 * ((k0 + 63) / 64);

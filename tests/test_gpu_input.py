@@ -150,6 +150,25 @@ def test_expand_row_tails(n, k_raw):
     test_expand_edges(n, k_raw, 70)
 
 
+def test_expand_most_rows():
+    """As many rows as the argument holds (rounding their number up to tiles
+    must not pass 2^31)."""
+    torch = torch_cuda()
+    n, seed = 2**31 - 1, 99
+    note(f"expand n={n}")
+    x = torch.empty((n, 1), dtype=torch.int8, device="cuda")
+    x.view(-1)[:] = 5
+    x[:3, 0] = torch.tensor([-1, 0, 127], dtype=torch.int8)
+    x[-3:, 0] = torch.tensor([0, -128, -3], dtype=torch.int8)
+    bits = B.expand(x, 64, seed)
+    few = torch.cat([x[:3], x[-3:], x[5:6]])
+    want = ob.expand(few.cpu().numpy(), ob.expansion_matrix(seed, 1, 64))
+    rows = pack_np(want, 1).view(np.int64)
+    np.testing.assert_array_equal(torch.cat([bits[:3], bits[-3:]]).cpu().numpy(), rows[:6])
+    for i in range(3, n - 3, 2**27):   # all the others are alike
+        assert bool((bits[i:min(i + 2**27, n - 3)] == int(rows[6, 0])).all())
+
+
 def test_training_on_expanded_inputs():
     torch = torch_cuda()
     p = Pair((256, 128), 5, 15, 64, 64, 0.25, seed=3)
