@@ -111,7 +111,8 @@ __global__ __launch_bounds__(64 * kRowWaves) void fwd_rows_kernel(const uint64_t
 // 27.2 us, 1024: 29.6 -> 29.2, 4096: 32.4 -> 28.4, 8192: 49.0 -> 28.0; four
 // patterns, 8192: 49.6 -> 31.4; a launch of 4096 x 4096 takes 5.0 -> 2.6 us.
 // Eight patterns took 29.7 -> 32.6 at 1024 and 50.4 -> 46.4 at 8192 (z of
-// eight patterns and rows in 64 registers), so the line lies at four.
+// eight patterns and rows in 64 registers; five to seven were not timed), so
+// the line lies at four.
 bool fwd_rows_wins(const FwdArgs &a) {
   return a.M <= kFwdRowsMax && ((a.mode == kFwdPlain && a.nslices == 1 && a.words_out > 0) ||
                                 (a.mode == kFwdWriteZ32 && a.words_out == 0));
